@@ -12,13 +12,14 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libwhitematter.so")
-# source -> extra flags. The projection GEMMs keep their accumulators in arch
+# source -> extra flags. The projection GEMMs and the matrix-core decode keep their accumulators in arch
 # VGPRs (MFMA VGPR form): their epilogue reads the accumulators in place, where
 # AGPR accumulators would be copied out all at once at the end of the K loop.
 SOURCES = {
     "wm_api.hip": [],
     "wm_pool.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "wm_attend.hip": [],
+    "wm_decode.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "wm_backward.hip": [],
     "wm_grad.hip": [],
     "wm_calib.hip": [],

@@ -15,10 +15,8 @@
 // row-major in LDS; bf16 V blocks too, read as V^T fragments with the transposing
 // LDS read (fp32 V is stored transposed).
 //
-// Decode form (attend_decode + combine): split-S over the cache, one
-// workgroup per (split, channel, sequence, KV head) serving every query row
-// that reads that channel and head (all its consumer layers, grouped query
-// heads and new tokens), so each channel slice is streamed from HBM once.
+// The decode form (split-S over the cache) is in wm_decode.hip.
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -40,8 +38,6 @@ __device__ __forceinline__ f32x8 ld_frag_4_4<float>(const float* p0, const float
   f32x4 a = *(const f32x4*)p0, b = *(const f32x4*)p1;
   return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
 }
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // A lane's sum of 16 softmax weights above this (some weight above 2^12) triggers the
 // rescale of the running state; `!(ps <= kGrowSum)` also catches inf and NaN.
@@ -65,14 +61,6 @@ __device__ __forceinline__ float ref_rescale(float growth, float m) {
   return m == kNoRef ? 0.f : fast_exp2(-growth);
 }
 
-// Document mask (packed sequences, Section 4.1): query i of sequence b, at position
-// ctx + i, reads cached slots from its document's first position on (clamped into
-// [0, position]); the dummy slot stays visible. Without a document array every row
-// starts at slot 0.
-__device__ __forceinline__ int doc_first(const int32_t* doc, int b, int T_new, int i, int pos) {
-  if (!doc) return 0;
-  return min(max(doc[(long)b * T_new + i], 0), pos);
-}
 __device__ __forceinline__ int wave_min_i(int v) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) v = min(v, __shfl_xor(v, m, 64));
@@ -1212,317 +1200,6 @@ void launch_attend_prefill(const Shape& sh, const LayerTable& chan_map, const T*
     hipLaunchKernelGGL((attend_prefill_kernel<T, 32>), grid, dim3(NT), 0, s, a);
 }
 
-// ------------------------------------------------------------------ decode
-// Cache slots per split workgroup: long splits amortise a workgroup's set-up and its
-// partial-state write; they are halved (down to 256) while the grid of splits x
-// (channel, sequence, KV head) would hold fewer than kDecodeMinBlocks workgroups.
-constexpr int kSplitMax = 4096, kSplitMin = 256;
-constexpr long kDecodeMinBlocks = 4096;
-
-int decode_split_len(const Shape& sh) {
-  const long kend = (long)sh.ctx_max + sh.span();  // upper bound on visible slots
-  const long slices = (long)sh.k * sh.B * sh.Hkv;
-  int len = kSplitMax;
-  while (len > kSplitMin && slices * ((kend + len - 1) / len) < kDecodeMinBlocks) len /= 2;
-  return len;
-}
-
-int decode_splits(const Shape& sh) {
-  const long kend = (long)sh.ctx_max + sh.span();
-  const int len = decode_split_len(sh);
-  int n = (int)((kend + len - 1) / len);
-  return n < 1 ? 1 : n;
-}
-
-size_t decode_partials_bytes(const Shape& sh) {
-  size_t rows = (size_t)sh.L * sh.B * sh.Hq * sh.T_new;
-  return rows * decode_splits(sh) * (sh.d + 2) * sizeof(float);
-}
-
-template <typename T> struct DecodeArgs {
-  const T *Q, *Kc, *Vc, *Kd, *Vd;
-  const int32_t* ctx_len;
-  const int32_t* doc;  // [B][T_new] first position of each token's document, or null
-  float* part;  // [L][B][Hq][T_new][nsplit][d + 2]: unnormalised o, m, l
-  T* O;
-  int B, T_new, L, Hq, Hkv, S_cap, mask_paper, nsplit, split_len;
-  int gs, gq, ctx_hi;  // query i of sequence b sits at position ctx_len[b] + gq + gs i
-  float scale_log2;
-  LayerTable chan;
-  ChannelGroups cg;
-};
-
-// Merge online-softmax state (m2, l2, o2) into (m, l, o).
-__device__ __forceinline__ void merge_state(float& m, float& l, float* o, float m2, float l2,
-                                            const float* o2, int n, float c) {
-  float M = fmaxf(m, m2);
-  float a1 = fast_exp2((m - M) * c), a2 = fast_exp2((m2 - M) * c);
-  l = l * a1 + l2 * a2;
-  for (int i = 0; i < n; ++i) o[i] = o[i] * a1 + o2[i] * a2;
-  m = M;
-}
-
-template <typename T, int DH, int NG>
-__global__ __launch_bounds__(256) void attend_decode_kernel(DecodeArgs<T> a) {
-  // A cache slot is read by CPS lanes of 8 elements each, in a group of LPS lanes (CPS
-  // rounded up to a power of two, so the group's sums are butterflies); lanes c8 >= CPS
-  // of a group load nothing and hold zeros (head dim 96: 12 of 16 lanes work).
-  constexpr int CPS = DH / 8;
-  constexpr int LPS = CPS <= 4 ? 4 : CPS <= 8 ? 8 : 16;
-  static_assert(LPS >= CPS && DH % 8 == 0, "8-element chunks in a power-of-two group");
-  constexpr int SPW = 64 / LPS;  // slots per wave per sweep step
-  constexpr int U = NG <= 2 ? 2 : 1;  // sweep steps per batch (U slots per lane)
-  constexpr int SPB = 4 * SPW * U;  // slots per batch of the 4 waves
-  __shared__ float red[4][NG][DH + 2];
-
-  const int split = blockIdx.x;
-  int y = blockIdx.y;
-  const int kvh = y % a.Hkv;
-  y /= a.Hkv;
-  const int b = y % a.B, c = y / a.B;
-  const int off = a.cg.offsets[c], nmem = a.cg.offsets[c + 1] - off;
-  if (nmem == 0) return;
-  const int grp = a.Hq / a.Hkv;
-  const int G = nmem * grp * a.T_new;
-  // position of query i: pos0 + gs i (wave-uniform)
-  const int pos0 = __builtin_amdgcn_readfirstlane(ctx_at(a.ctx_len, b, a.ctx_hi)) + a.gq;
-  const int gs = a.gs;
-  const int incl = a.mask_paper ? 0 : 1;
-  const int kend = min(pos0 + gs * (a.T_new - 1) + incl, a.S_cap);
-  const int s0 = split * a.split_len, s1 = min(s0 + a.split_len, kend);
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int sg = lane / LPS, c8 = lane % LPS;
-  const float cl2 = a.scale_log2;
-  const float thresh = 8.0f / cl2;  // log2 headroom before a rescale
-
-  const long cbase = (((long)c * a.B + b) * a.Hkv + kvh) * (long)a.S_cap * DH;
-  // the slice through buffer views: slots at or past s1 read zeros without a branch
-  const __amdgpu_buffer_rsrc_t kview = make_view(a.Kc + cbase, (uint32_t)a.S_cap * DH * sizeof(T));
-  const __amdgpu_buffer_rsrc_t vview = make_view(a.Vc + cbase, (uint32_t)a.S_cap * DH * sizeof(T));
-  const bool chunk = c8 < CPS;  // the lane holds 8 channels of the head
-  auto slot_off = [&](int s) {
-    return s < s1 && chunk ? (uint32_t)(s * DH + 8 * c8) * (uint32_t)sizeof(T) : kOffOob;
-  };
-
-  for (int g0 = 0; g0 < G; g0 += NG) {
-    const int ng = min(NG, G - g0);
-    float q[NG][8], m[NG], ls[NG], o[NG][8];
-    int vis[NG], lov[NG];  // the row reads slots lov <= s < vis
-#pragma unroll
-    for (int gi = 0; gi < NG; ++gi) {
-      m[gi] = kNegBig;
-      ls[gi] = 0.f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) o[gi][i] = 0.f;
-      if (gi < ng) {
-        int g = g0 + gi;
-        int i = g % a.T_new, gq = (g / a.T_new) % grp, mi = g / (a.T_new * grp);
-        int l = a.cg.members[off + mi], hq = kvh * grp + gq;
-        long rowid = (((long)l * a.B + b) * a.Hq + hq) * a.T_new + i;
-        vis[gi] = pos0 + gs * i + incl;
-        lov[gi] = doc_first(a.doc, b, a.T_new, i, pos0 + gs * i);
-        if (chunk) load8(a.Q + rowid * DH + 8 * c8, q[gi]);
-        else {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) q[gi][i] = 0.f;
-        }
-      } else {
-        vis[gi] = 0;
-        lov[gi] = 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) q[gi][i] = 0.f;
-      }
-    }
-
-    // raw K/V fragments of a batch (U slots per lane), double-buffered across batches
-    // (two batches per loop trip keep the buffer indices static)
-    frag_t<T> kr0[U], vr0[U], kr1[U], vr1[U];
-    auto fetch = [&](int sb, frag_t<T>* kr, frag_t<T>* vr) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t so = slot_off(sb + w * SPW * U + u * SPW + sg);
-        kr[u] = buf_frag<T>(kview, so);
-        vr[u] = buf_frag<T>(vview, so);
-      }
-    };
-    auto consume = [&](int sb, const frag_t<T>* kr, const frag_t<T>* vr) {
-      float p[U][NG];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int s = sb + w * SPW * U + u * SPW + sg;
-#pragma unroll
-        for (int gi = 0; gi < NG; ++gi) {
-          float d = 0.f;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) d += q[gi][i] * to_f32(kr[u][i]);
-#pragma unroll
-          for (int x = 1; x < LPS; x <<= 1) d += __shfl_xor(d, x, 64);
-          p[u][gi] = s < s1 && s < vis[gi] && s >= lov[gi] ? d : kNegBig;
-        }
-      }
-#pragma unroll
-      for (int gi = 0; gi < NG; ++gi) {
-        float mx = p[0][gi];
-#pragma unroll
-        for (int u = 1; u < U; ++u) mx = fmaxf(mx, p[u][gi]);
-        if (mx > m[gi] + thresh) {  // lazy rescale (per lane; merged exactly below)
-          const float al = fast_exp2((m[gi] - mx) * cl2);
-          ls[gi] *= al;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) o[gi][i] *= al;
-          m[gi] = mx;
-        }
-        const float mc = m[gi] * cl2;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const float pe = p[u][gi] > 0.5f * kNegBig ? fast_exp2(p[u][gi] * cl2 - mc) : 0.f;
-          ls[gi] += pe;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) o[gi][i] += pe * to_f32(vr[u][i]);
-        }
-      }
-    };
-    // batches past the split read zeros (and are masked), so the loop runs in pairs
-    fetch(s0, kr0, vr0);
-    for (int sb = s0; sb < s1; sb += 2 * SPB) {
-      fetch(sb + SPB, kr1, vr1);
-      consume(sb, kr0, vr0);
-      fetch(sb + 2 * SPB, kr0, vr0);
-      consume(sb + SPB, kr1, vr1);
-    }
-    // merge the slot groups of the wave (lanes that share c8)
-#pragma unroll
-    for (int msk = LPS; msk < 64; msk <<= 1)
-#pragma unroll
-      for (int gi = 0; gi < NG; ++gi) {
-        float m2 = __shfl_xor(m[gi], msk, 64), l2 = __shfl_xor(ls[gi], msk, 64), o2[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) o2[i] = __shfl_xor(o[gi][i], msk, 64);
-        merge_state(m[gi], ls[gi], o[gi], m2, l2, o2, 8, cl2);
-      }
-    if (sg == 0 && chunk) {
-#pragma unroll
-      for (int gi = 0; gi < NG; ++gi) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) red[w][gi][8 * c8 + i] = o[gi][i];
-        if (c8 == 0) {
-          red[w][gi][DH] = m[gi];
-          red[w][gi][DH + 1] = ls[gi];
-        }
-      }
-    }
-    __syncthreads();
-    for (int e = tid; e < ng * DH; e += 256) {
-      int gi = e / DH, dd = e % DH;
-      float M = kNegBig;
-      for (int ww = 0; ww < 4; ++ww) M = fmaxf(M, red[ww][gi][DH]);
-      float Lsum = 0.f, Osum = 0.f;
-      for (int ww = 0; ww < 4; ++ww) {
-        float sc = fast_exp2((red[ww][gi][DH] - M) * cl2);
-        Lsum += red[ww][gi][DH + 1] * sc;
-        Osum += red[ww][gi][dd] * sc;
-      }
-      // recompute the row id for gi (registers are per-lane; rows are uniform)
-      int g = g0 + gi;
-      int i = g % a.T_new, gq = (g / a.T_new) % grp, mi = g / (a.T_new * grp);
-      int l = a.cg.members[off + mi], hq = kvh * grp + gq;
-      long rid = (((long)l * a.B + b) * a.Hq + hq) * a.T_new + i;
-      float* dst = a.part + (rid * a.nsplit + split) * (DH + 2);
-      dst[dd] = Osum;
-      if (dd == 0) {
-        dst[DH] = M;
-        dst[DH + 1] = Lsum;
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// One wave per query row: fold the dummy slot and all split partials.
-template <typename T, int DH>
-__global__ __launch_bounds__(256) void attend_combine_kernel(DecodeArgs<T> a) {
-  constexpr int EPL = (DH + 63) / 64;  // elements per lane: channel 64 e + lane
-  const long rows = (long)a.L * a.B * a.Hq * a.T_new;
-  const long rid = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (rid >= rows) return;
-  long t = rid;
-  const int i = (int)(t % a.T_new);
-  t /= a.T_new;
-  const int hq = (int)(t % a.Hq);
-  t /= a.Hq;
-  const int b = (int)(t % a.B), l = (int)(t / a.B);
-  const int c = a.chan.v[l], kvh = hq / (a.Hq / a.Hkv);
-  const float cl2 = a.scale_log2;
-
-  float M, Lsum, o[EPL];
-  auto active = [&](int e) { return 64 * e + lane < DH; };
-  if (a.mask_paper) {
-    const T* q = a.Q + rid * DH;
-    const T* kd = a.Kd + ((long)c * a.Hkv + kvh) * DH;
-    const T* vd = a.Vd + ((long)c * a.Hkv + kvh) * DH;
-    float part = 0.f;
-    for (int e = 0; e < EPL; ++e)
-      if (active(e)) part += to_f32(q[64 * e + lane]) * to_f32(kd[64 * e + lane]);
-    M = wave_sum(part);
-    Lsum = 1.f;
-    for (int e = 0; e < EPL; ++e) o[e] = active(e) ? to_f32(vd[64 * e + lane]) : 0.f;
-  } else {
-    M = kNegBig;
-    Lsum = 0.f;
-    for (int e = 0; e < EPL; ++e) o[e] = 0.f;
-  }
-  const float* src = a.part + rid * a.nsplit * (DH + 2);
-  for (int sidx = 0; sidx < a.nsplit; ++sidx) {
-    const float* ps = src + (long)sidx * (DH + 2);
-    float o2[EPL];
-    for (int e = 0; e < EPL; ++e) o2[e] = active(e) ? ps[64 * e + lane] : 0.f;
-    merge_state(M, Lsum, o, ps[DH], ps[DH + 1], o2, EPL, cl2);
-  }
-  T* dst = a.O + ((((long)l * a.B + b) * a.T_new + i) * a.Hq + hq) * DH;
-  for (int e = 0; e < EPL; ++e)
-    if (active(e)) dst[64 * e + lane] = from_f32<T>(o[e] / Lsum);
-}
-
-template <typename T, int DH>
-static void decode_dispatch(const DecodeArgs<T>& a, int G, dim3 grid, hipStream_t s) {
-  if (G <= 1)
-    hipLaunchKernelGGL((attend_decode_kernel<T, DH, 1>), grid, dim3(256), 0, s, a);
-  else if (G <= 2)
-    hipLaunchKernelGGL((attend_decode_kernel<T, DH, 2>), grid, dim3(256), 0, s, a);
-  else if (G <= 4)
-    hipLaunchKernelGGL((attend_decode_kernel<T, DH, 4>), grid, dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((attend_decode_kernel<T, DH, 8>), grid, dim3(256), 0, s, a);
-  long rows = (long)a.L * a.B * a.Hq * a.T_new;
-  hipLaunchKernelGGL((attend_combine_kernel<T, DH>), dim3((unsigned)((rows + 3) / 4)), dim3(256),
-                     0, s, a);
-}
-
-template <typename T>
-void launch_attend_decode(const Shape& sh, const LayerTable& chan_map, const ChannelGroups& cg,
-                          const T* Q, const T* Kc, const T* Vc, const T* Kd, const T* Vd,
-                          const int32_t* ctx_len, const int32_t* doc, float* partials, T* O,
-                          hipStream_t s) {
-  if (sh.N() <= 0) return;
-  DecodeArgs<T> a{Q, Kc, Vc, Kd, Vd, ctx_len, doc, partials, O, sh.B, sh.T_new, sh.L, sh.Hq, sh.Hkv,
-                  sh.S_cap, sh.mask_paper, decode_splits(sh), decode_split_len(sh), sh.gs, sh.gq,
-                  sh.ctx_hi, kLog2e / sqrtf((float)sh.d), chan_map, cg};
-  int maxmem = 0;
-  for (int c = 0; c < sh.k; ++c) {
-    int n = cg.offsets[c + 1] - cg.offsets[c];
-    if (n > maxmem) maxmem = n;
-  }
-  int G = maxmem * (sh.Hq / sh.Hkv) * sh.T_new;
-  dim3 grid(a.nsplit, sh.Hkv * sh.B * sh.k);
-  if (sh.d == 96) {
-    if constexpr (sizeof(T) == 2) decode_dispatch<T, 96>(a, G, grid, s);
-  } else if (sh.d == 64)
-    decode_dispatch<T, 64>(a, G, grid, s);
-  else
-    decode_dispatch<T, 32>(a, G, grid, s);
-}
-
 // ------------------------------------------------------------ dense soft read
 // Layer l's soft mix of the k channels (the dense read of Section 3.1 Step 3):
 // Kl[l][b][h][s] = sum_c w[l][c] Kc[c][b][h][s], the same for V, over the slots the
@@ -1602,9 +1279,6 @@ void launch_soft_read(const Shape& sh, const float* w, const T* Kc, const T* Vc,
   template void launch_attend_prefill<T>(const Shape&, const LayerTable&, const T*, const T*,   \
                                          const T*, const T*, const T*, const int32_t*,          \
                                          const int32_t*, T*, void*, hipStream_t);               \
-  template void launch_attend_decode<T>(const Shape&, const LayerTable&, const ChannelGroups&,  \
-                                        const T*, const T*, const T*, const T*, const T*,       \
-                                        const int32_t*, const int32_t*, float*, T*, hipStream_t); \
   template void launch_soft_read<T>(const Shape&, const float*, const T*, const T*, const T*,   \
                                     const T*, const int32_t*, T*, T*, T*, T*, hipStream_t);
 WM_INST(float)

@@ -181,6 +181,17 @@ __device__ __forceinline__ int ctx_at(const int32_t* ctx_len, int b, int hi) {
   return ctx_len ? min(max(ctx_len[b], 0), hi) : 0;
 }
 
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Document mask (packed sequences, Section 4.1): query i of sequence b, at position
+// ctx + i, reads cached slots from its document's first position on (clamped into
+// [0, position]); the dummy slot stays visible. Without a document array every row
+// starts at slot 0.
+__device__ __forceinline__ int doc_first(const int32_t* doc, int b, int T_new, int i, int pos) {
+  if (!doc) return 0;
+  return min(max(doc[(long)b * T_new + i], 0), pos);
+}
+
 __device__ __forceinline__ f32x16 zero16() {
   f32x16 z;
 #pragma unroll
