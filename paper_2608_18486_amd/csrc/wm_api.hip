@@ -251,7 +251,8 @@ Layout layout(const wm_dims& dd, int op) {
   if (op == WM_OP_Q_PROJECT || all || layer) Ly.wq = take(wm::q_fold_elems(make_shape(d)) * es);
   if (op == WM_OP_ROUTER_MIX || all || pool) {
     Ly.wa = take(wm::router_fold_elems(make_shape(d)) * es);
-    Ly.rpart = take(wm::router_partials_bytes(make_shape(d)));
+    Ly.rpart = take(std::max(wm::router_partials_bytes(make_shape(d)),
+                             op == WM_OP_ROUTER_MIX ? 0 : wm::few_router_bytes(make_shape(d))));
   }
   Ly.total = N == 0 ? 0 : off;
   return Ly;
@@ -413,6 +414,13 @@ template <typename T>
 void run_kv_project(const wm_dims& d, const wm_params& P, const T* mixed, const int32_t* ctx_len,
                     T* Kc, T* Vc, void* ws, hipStream_t s) {
   wm::Shape sh = make_shape(d);
+  if constexpr (sizeof(T) == 2) {
+    if (wm::few_tokens(sh)) {
+      wm::launch_few_kv(sh, mixed, (const T*)P.g_mid, (const T*)P.Wk, (const T*)P.Wv,
+                        (const T*)P.g_knorm, ctx_len, Kc, Vc, s);
+      return;
+    }
+  }
   Layout Ly = layout(d, WM_OP_KV_PROJECT);
   float* rinv_mid = (float*)at(ws, Ly.rinv_mid);
   float* tab = (float*)at(ws, Ly.tab);
@@ -427,6 +435,13 @@ template <typename T>
 void run_q_project(const wm_dims& d, const wm_params& P, const T* H, const int32_t* ctx_len, T* Q,
                    void* ws, hipStream_t s) {
   wm::Shape sh = make_shape(d);
+  if constexpr (sizeof(T) == 2) {
+    if (wm::few_tokens(sh)) {
+      wm::launch_few_queries(sh, H, (const T*)P.g_in, (const T*)P.Wq, (const T*)P.g_qnorm,
+                             ctx_len, Q, 0, d.L, s);
+      return;
+    }
+  }
   Layout Ly = layout(d, WM_OP_Q_PROJECT);
   float* rinv = (float*)at(ws, Ly.rinv);
   float* tab = (float*)at(ws, Ly.tab);
@@ -450,6 +465,21 @@ void run_attend(const wm_dims& d, const wm_params& P, const T* Q, const int32_t*
                                  O, (uint32_t*)part, s);
 }
 
+// Steps 1-2 for few bf16 tokens (see wm_few.hip): no norms, table or folded weights.
+void run_few_pool(const wm_dims& d, const wm::Shape& sh, const wm_params& P, const bf16* H,
+                  const int32_t* ctx_len, bf16* Kc, bf16* Vc, const Layout& Ly, void* ws,
+                  hipStream_t s, void* const* events = nullptr) {
+  float* part = (float*)at(ws, Ly.rpart);
+  bf16* mixed = (bf16*)at(ws, Ly.mixed);
+  wm::launch_few_router(sh, router_layers(d).v[0], H, (const bf16*)P.g_pre,
+                        (const bf16*)P.W_alpha, part, s);
+  if (events) (void)hipEventRecord((hipEvent_t)events[2], s);
+  wm::launch_few_mix(sh, H, (const bf16*)P.g_pre, (const bf16*)P.b_alpha, part, mixed, s);
+  if (events) (void)hipEventRecord((hipEvent_t)events[3], s);
+  wm::launch_few_kv(sh, mixed, (const bf16*)P.g_mid, (const bf16*)P.Wk, (const bf16*)P.Wv,
+                    (const bf16*)P.g_knorm, ctx_len, Kc, Vc, s);
+}
+
 template <typename T>
 int run_layer_step(const wm_dims& d, const wm_params& P, const T* H, const int32_t* chan_map,
                    const int32_t* ctx_len, const int32_t* doc, T* Kc, T* Vc, T* O, void* ws,
@@ -465,6 +495,20 @@ int run_layer_step(const wm_dims& d, const wm_params& P, const T* H, const int32
   float* rinv_mid = (float*)at(ws, Ly.rinv_mid);
   float* tab = (float*)at(ws, Ly.tab);
   T* Q = (T*)at(ws, Ly.q);
+  if constexpr (sizeof(T) == 2) {
+    if (wm::few_tokens(sh)) {
+      mark(0);
+      mark(1);
+      run_few_pool(d, sh, P, H, ctx_len, Kc, Vc, Ly, ws, s, events);
+      mark(4);
+      wm::launch_few_queries(sh, H, (const T*)P.g_in, (const T*)P.Wq, (const T*)P.g_qnorm,
+                             ctx_len, Q, 0, d.L, s);
+      mark(5);
+      run_attend<T>(d, P, Q, chan_map, ctx_len, doc, Kc, Vc, O, (float*)at(ws, Ly.part), s);
+      mark(6);
+      return WM_OK;
+    }
+  }
   mark(0);
   wm::launch_row_rms<T>(H, (long)sh.N() * sh.L, sh.D, sh.eps, rinv, s);
   wm::launch_rope_table(sh, ctx_len, tab, s);
@@ -495,6 +539,12 @@ void run_pool(const wm_dims& d, const wm_params& P, const T* H, const int32_t* c
               T* Vc, const Layout& Ly, void* ws, hipStream_t s, bool have_rinv, bool have_tab,
               bool prefolded) {
   wm::Shape sh = make_shape(d);
+  if constexpr (sizeof(T) == 2) {
+    if (wm::few_tokens(sh)) {
+      run_few_pool(d, sh, P, H, ctx_len, Kc, Vc, Ly, ws, s);
+      return;
+    }
+  }
   float* rinv = (float*)at(ws, Ly.rinv);
   float* alpha = (float*)at(ws, Ly.alpha);
   T* mixed = (T*)at(ws, Ly.mixed);
@@ -524,11 +574,20 @@ void run_layer_attend(const wm_dims& d, const wm_params& P, int l, const T* H,
   float* tab = (float*)at(ws, Ly.tab);
   T* Q = (T*)at(ws, Ly.q);
   T* wq = (T*)at(ws, Ly.wq);
-  wm::launch_row_rms_strided<T>(H + (long)l * sh.D, sh.N(), sh.D, (long)sh.L * sh.D, sh.L, sh.eps,
-                                rinv + l, s);
-  if (!have_tab) wm::launch_rope_table(sh, ctx_len, tab, s);
-  if (!q_prefolded) wm::launch_q_fold<T>(sh, (const T*)P.g_in, (const T*)P.Wq, wq, l, 1, s);
-  wm::launch_q_layers<T>(sh, H, rinv, (const T*)P.g_qnorm, tab, Q, wq, l, 1, s);
+  bool few = false;
+  if constexpr (sizeof(T) == 2) {
+    few = wm::few_tokens(sh);
+    if (few)
+      wm::launch_few_queries(sh, H, (const T*)P.g_in, (const T*)P.Wq, (const T*)P.g_qnorm,
+                             ctx_len, Q, l, 1, s);
+  }
+  if (!few) {
+    wm::launch_row_rms_strided<T>(H + (long)l * sh.D, sh.N(), sh.D, (long)sh.L * sh.D, sh.L,
+                                  sh.eps, rinv + l, s);
+    if (!have_tab) wm::launch_rope_table(sh, ctx_len, tab, s);
+    if (!q_prefolded) wm::launch_q_fold<T>(sh, (const T*)P.g_in, (const T*)P.Wq, wq, l, 1, s);
+    wm::launch_q_layers<T>(sh, H, rinv, (const T*)P.g_qnorm, tab, Q, wq, l, 1, s);
+  }
   const wm::Shape sh1 = one_layer(sh);
   wm::LayerTable mt{};
   mt.v[0] = chan_map[l];

@@ -562,20 +562,25 @@ static void decode_mfma(DecodeArgs<bf16> a, int G, const Shape& sh, hipStream_t 
   const dim3 grid(a.nsplit, sh.Hkv * sh.B * sh.k, z);
   // a cache read once by one row tile, and larger than the caches keep from call to call
   const bool once = z == 1 && 4L * sh.k * sh.B * sh.Hkv * kend * DH >= kDecodeStreamBytes;
-  // 4 waves per workgroup; at head dim 64, 2 where all workgroups of 2 (5 per CU) then run
-  // at once: 4 would leave a part round (2 per CU). Attention alone, 2 / 4 waves, us:
-  // 768 workgroups 122 / 131 (B 4, ctx 4000, L 24, k 12), 576 31.8 / 35.8 (B 2, T_new 2, ctx
-  // 2000, L 12), but 2304 156 / 143 (B 16, ctx 1500, L 12).
-  const bool two = DH == 64 && (long)a.nsplit * sh.k * sh.B * sh.Hkv * z <= 5L * device_cus();
+  // Waves per workgroup: 2, which leaves a CU's LDS to five workgroups (three at head dim
+  // 96); 1 where a workgroup's walk is at most 128 slots (four blocks); 4 at head dim 96
+  // where the workgroups do not outnumber the CUs, and at head dim 64 for long walks in
+  // several rounds of workgroups. Attention alone with 1 / 2 / 4 waves, us: ctx 100, B 64, L 24, k 12,
+  // heads of 64: 77 / 87 / 111; ctx 4000, B 4: 172 / 126 / 133; ctx 1500, B 16, L 12: 144 /
+  // 156 / 144; ctx 3000, B 24: 426 / 424 / 400; heads of 96, k = 8: ctx 1000, B 4: 19 / 16.7 /
+  // 18.7; ctx 8000, B 1, k = 2: 31 / 26 / 23.6.
+  const long wgs = (long)a.nsplit * sh.k * sh.B * sh.Hkv * z, per = std::min<long>(kend, len);
+  const int waves = per <= 128 ? 1
+                    : (DH == 96 ? wgs <= device_cus() : wgs > 5L * device_cus() && per >= 1024)
+                        ? 4 : 2;
 #define WM_DEC_GO(NW, DOC, ONCE)                                                              \
   hipLaunchKernelGGL((attend_decode_mfma_kernel<DH, NW, DOC, ONCE>), grid, dim3(64 * (NW)), 0, \
                      s, a)
 #define WM_DEC_NW(DOC, ONCE)                                                                   \
   do {                                                                                         \
-    if constexpr (DH == 64) {                                                                  \
-      if (two) WM_DEC_GO(2, DOC, ONCE);                                                        \
-      else WM_DEC_GO(4, DOC, ONCE);                                                            \
-    } else WM_DEC_GO(4, DOC, ONCE);                                                            \
+    if (waves == 1) WM_DEC_GO(1, DOC, ONCE);                                                   \
+    else if (waves == 2) WM_DEC_GO(2, DOC, ONCE);                                              \
+    else WM_DEC_GO(4, DOC, ONCE);                                                              \
   } while (0)
   if (a.doc) {
     if (once) WM_DEC_NW(true, true);

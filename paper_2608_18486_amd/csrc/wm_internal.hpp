@@ -92,6 +92,24 @@ template <typename T>
 void launch_q_layers(const Shape& sh, const T* H, const float* rinv, const T* g_qnorm,
                      const float* rope_tab, T* Q, const T* wfold, int l0, int nl, hipStream_t s);
 
+// -- few tokens (bf16, head dims 64 and 96; wm_few.hip) -------------------------------
+// The pool and the queries of at most kFewRows tokens without folded weights, norms or angle
+// table in the workspace: the router's partial sums (few_router_bytes), the mix, the K/V and
+// query projections, each one launch.
+constexpr int kFewRows = 32;
+bool few_tokens(const Shape& sh);
+size_t few_router_bytes(const Shape& sh);
+void launch_few_router(const Shape& sh, int s0, const bf16* H, const bf16* g_pre,
+                       const bf16* W_alpha, float* part, hipStream_t s);
+void launch_few_mix(const Shape& sh, const bf16* H, const bf16* g_pre, const bf16* b_alpha,
+                    const float* part, bf16* mixed, hipStream_t s);
+void launch_few_kv(const Shape& sh, const bf16* mixed, const bf16* g_mid, const bf16* Wk,
+                   const bf16* Wv, const bf16* g_knorm, const int32_t* ctx_len, bf16* Kc,
+                   bf16* Vc, hipStream_t s);
+void launch_few_queries(const Shape& sh, const bf16* H, const bf16* g_in, const bf16* Wq,
+                        const bf16* g_qnorm, const int32_t* ctx_len, bf16* Q, int l0, int nl,
+                        hipStream_t s);
+
 // -- pass driver (Section 3.3) --------------------------------------------------
 // The stand-in decoder block: out[n] = h[n] + W o_l[n] (W [D][HD], o_l [M][HD]); rows of h
 // and out strided by hs and os elements.

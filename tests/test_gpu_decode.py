@@ -1,6 +1,6 @@
 """GPU parity of the bf16 decode attention on the matrix cores (Section 3.1 Step 3, Section
 3.2) at the edges of its tiles: 32 rows (consumers x grouped heads x new tokens) per tile,
-32-slot blocks dealt to four waves, splits of at least 256 slots, and ragged sequences that
+32-slot blocks dealt to one, two or four waves, splits of at least 256 slots, and ragged sequences that
 leave waves and whole splits without a slot. Against the oracle, with the repository's bf16
 bounds."""
 import pytest
@@ -8,7 +8,8 @@ import torch
 
 import oracle
 from tests import synth
-from tests.parity import _bias, _dev, _f64, _gdims, _odims, check_close, wm  # noqa: F401
+from tests.parity import (_bias, _check_cache, _dev, _f64, _gdims, _odims,  # noqa: F401
+                          check_close, wm)
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +38,35 @@ def test_decode_row_and_slot_edges(wm, d, mask_mode, L, Hq, Hkv, T_new, ctx):
     torch.cuda.synchronize()
     check_close(O, ref, "bf16", "decode d%d mask%d rows %d ctx %d"
                 % (d, mask_mode, L * Hq // Hkv * T_new, ctx))
+
+
+@pytest.mark.parametrize("d", [64, 96])
+@pytest.mark.parametrize("mode", ["linear", "softmax", "static", "nofeedback"])
+@pytest.mark.parametrize("B,T_new,D,p,ctx", [(1, 1, 32, 1, 0),      # waves without a share of K
+                                             (5, 1, 160, 2, 37),   # a part batch of columns
+                                             (31, 1, 64, 1, 70),
+                                             (8, 4, 544, 3, 70),   # 32 tokens
+                                             (11, 3, 96, 1, 9)])   # 33: the many-token path
+def test_few_token_step(wm, d, mode, B, T_new, D, p, ctx):
+    """The few-token pool and queries (router, mix, K/V and query projections of at most 32
+    bf16 tokens) through the fused step, at uneven widths, against the oracle."""
+    L = 4 if mode == "nofeedback" else 5
+    k = L if mode == "nofeedback" else 3
+    w = synth.small("few_%s" % mode, B=B, T_new=T_new, L=L, k=k, D=D, Hq=4, Hkv=2, d=d, ctx=ctx,
+                    dtype="bf16", p=p)
+    print("few tokens d%d %s B%d T%d D%d p%d" % (d, mode, B, T_new, D, p), flush=True)
+    P = synth.make_params(w, torch.as_tensor(_bias(w)) + 0.2, gains="random")
+    H = synth.make_states(w)
+    K0, V0 = synth.make_cache_cpu(w)
+    ctx_len = synth.make_ctx_len(w, ragged=True)
+    opts = dict(mix_mode=1 if mode == "softmax" else 0,
+                router_mode={"static": 1, "nofeedback": 2}.get(mode, 0))
+    Ko, Vo = _f64(K0).copy(), _f64(V0).copy()
+    Oo = oracle.layer_step(_odims(w, **opts), P, H, w.chan_map, ctx_len.numpy(), Ko, Vo)
+    Kg, Vg = K0.cuda(), V0.cuda()
+    O = torch.full((w.L, B, T_new, w.Hq * d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wm.layer_step(_gdims(wm, w, **opts), _dev(P), H.cuda(), w.chan_map, ctx_len.cuda(), Kg, Vg, O)
+    torch.cuda.synchronize()
+    _check_cache(Kg, Ko, K0, w, ctx_len.numpy(), "bf16", "K")
+    _check_cache(Vg, Vo, V0, w, ctx_len.numpy(), "bf16", "V")
+    check_close(O, Oo, "bf16", "few-token step %s" % mode)
