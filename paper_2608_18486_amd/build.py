@@ -20,6 +20,7 @@ SOURCES = {
     "wm_pool.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "wm_attend.hip": [],
     "wm_decode.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "wm_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "wm_few.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "wm_backward.hip": [],
     "wm_grad.hip": [],

@@ -558,20 +558,6 @@ __device__ __forceinline__ void pf_mask(f32x16& v, int i, int lim0, int lo0, int
   }
 }
 
-// Sum of the 16 bf16 weights of a lane, two dot products against (1, 1) per pair of
-// fragments' halves: the normaliser then adds exactly the weights the PV products use.
-__device__ __forceinline__ float pf_wsum(const bf16x8& a, const bf16x8& b) {
-  const bf16x2 one = {(bf16)1.f, (bf16)1.f};
-  float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const bf16x2 pa = {a[2 * e], a[2 * e + 1]}, pb = {b[2 * e], b[2 * e + 1]};
-    s0 = __builtin_amdgcn_fdot2_f32_bf16(pa, one, s0, false);
-    s1 = __builtin_amdgcn_fdot2_f32_bf16(pb, one, s1, false);
-  }
-  return s0 + s1;
-}
-
 // f(integral_constant<int, I>) for I = I0 .. N-1, in order.
 template <int I0, int N, class F> __device__ __forceinline__ void static_for(F& f) {
   if constexpr (I0 < N) {
@@ -677,7 +663,7 @@ __device__ __forceinline__ void pf_step(const char* sm, const PfLane<DH>& lo, ui
 // One query tile of the persistent kernel below: 32 QT rows per wave of one (consumer,
 // sequence, head). On entry every wave is past the previous tile (its copies have
 // landed and its ring reads are done) and the rings hold finite values.
-template <int QT, int DH, bool DOC, bool SPLIT>
+template <int QT, int DH, bool DOC, bool SPLIT, bool PAIR>
 __device__ __forceinline__ void pf_tile(const AttnArgs<bf16>& a, const int tile, const int split,
                                         char* smem, int* s_lo) {
   using P = PfDma<QT, DH>;
@@ -686,21 +672,23 @@ __device__ __forceinline__ void pf_tile(const AttnArgs<bf16>& a, const int tile,
   // head's group, query tile (longest first). Consecutive tiles read one channel's K/V
   // slice: every query tile and grouped head of a consumer, then the next consumer of
   // the same channel, so an XCD's L2 serves a slice to all its readers.
-  const int G = a.Hq / a.Hkv;
+  // With PAIR a workgroup takes two heads of the group and half the queries of each.
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = a.Hq / a.Hkv, GP = PAIR ? G / 2 : G;
   const int qtile = a.n_qtiles - 1 - tile % a.n_qtiles;
   int y = tile / a.n_qtiles;
-  const int hg = y % G;
-  y /= G;
+  const int hg = PAIR ? 2 * (y % GP) + (w >> 1) : y % GP;
+  y /= GP;
   const int li = y % a.L;
   y /= a.L;
   const int kvh = y % a.Hkv, b = y / a.Hkv;
   const int hq = kvh * G + hg, l = a.lord.v[li];
   const int c = a.chan.v[l];
-  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ctx = __builtin_amdgcn_readfirstlane(ctx_at(a.ctx_len, b, a.ctx_hi));
   const int incl = a.mask_paper ? 0 : 1;
-  const int q0 = qtile * P::BQ, qw0 = q0 + 32 * QT * w;
+  const int bq = PAIR ? P::BQ / 2 : P::BQ;  // queries per workgroup
+  const int q0 = qtile * bq, qw0 = q0 + 32 * QT * (PAIR ? w & 1 : w);
   const float cl2 = a.scale_log2;
   const int gs = a.gs, pos0 = ctx + a.gq;  // query i sits at position pos0 + gs i
 
@@ -771,7 +759,7 @@ __device__ __forceinline__ void pf_tile(const AttnArgs<bf16>& a, const int tile,
 
   const long cbase = (((long)c * a.B + b) * a.Hkv + kvh) * (long)a.S_cap * DH +
                      (long)base0 * DH;
-  const int qlast = min(q0 + P::BQ, a.T_new) - 1;
+  const int qlast = min(q0 + bq, a.T_new) - 1;
   const int scap = a.S_cap - base0;
   int kend = min(ctxr + gs * qlast + incl, scap);   // slots the workgroup may see
   if constexpr (SPLIT) {
@@ -993,8 +981,9 @@ __device__ __forceinline__ void pf_tile(const AttnArgs<bf16>& a, const int tile,
 // order, so the slow (long) tiles start first and the last ones are the shortest. With
 // queue null the grid has one workgroup per tile (tile order as above, XCD-aware).
 // DOC: the document mask is on (a.doc is not null); the kernel without it keeps the
-// step loop free of the document bookkeeping.
-template <int QT, int DH, bool DOC, bool SPLIT = false>
+// step loop free of the document bookkeeping. PAIR: a workgroup takes 64 queries of two heads
+// of a KV head.
+template <int QT, int DH, bool DOC, bool SPLIT = false, bool PAIR = false>
 __global__ __launch_bounds__(64 * kPfWaves) __attribute__((amdgpu_waves_per_eu(DH == 64 ? 3 : 2)))
 void attend_prefill_dma_kernel(AttnArgs<bf16> a, uint32_t* queue) {
   using P = PfDma<QT, DH>;
@@ -1012,16 +1001,24 @@ void attend_prefill_dma_kernel(AttnArgs<bf16> a, uint32_t* queue) {
     for (int k = 0; k < P::SMEM_BYTES / (16 * P::NT); ++k)
       *(i32x4*)(smem + 16 * (tid + P::NT * k)) = z;
   }
-  const int total = a.n_qtiles * a.Hq * a.B * a.L;
+  const int total = a.n_qtiles * (PAIR ? a.Hq / 2 : a.Hq) * a.B * a.L;
   if constexpr (SPLIT) {  // a workgroup per tile and split range (consecutive: one tile)
     __syncthreads();  // the zeroed rings are in place before any copy lands
     const int idx = xcd_tile(blockIdx.x, total * a.nsplit);
-    pf_tile<QT, DH, DOC, true>(a, idx / a.nsplit, idx % a.nsplit, smem, s_lo);
+    pf_tile<QT, DH, DOC, true, false>(a, idx / a.nsplit, idx % a.nsplit, smem, s_lo);
     return;
   }
   if (!queue) {  // a grid of one workgroup per tile (grids the CUs hold at once)
     __syncthreads();  // the zeroed rings are in place before any copy lands
-    pf_tile<QT, DH, DOC, false>(a, xcd_tile(blockIdx.x, total), 0, smem, s_lo);
+    int tile = xcd_tile(blockIdx.x, total);
+    const int units = total / a.n_qtiles;  // heads (pairs) x consumers x sequences
+    if (PAIR && units % kNumXcd == 0) {
+      // XCD x owns a contiguous band of the units and starts the longest tile of each first,
+      // so that a CU's second workgroup is a short one
+      const int px = units / kNumXcd, i = blockIdx.x / kNumXcd;
+      tile = ((blockIdx.x % kNumXcd) * px + i % px) * a.n_qtiles + i / px;
+    }
+    pf_tile<QT, DH, DOC, false, PAIR>(a, tile, 0, smem, s_lo);
     return;
   }
   const int nq = min((int)gridDim.x, kNumXcd), x = blockIdx.x % nq;
@@ -1032,7 +1029,7 @@ void attend_prefill_dma_kernel(AttnArgs<bf16> a, uint32_t* queue) {
   __syncthreads();  // also: the zeroed rings are in place before any copy lands
   int t = __builtin_amdgcn_readfirstlane(s_tile);
   while (t < count) {
-    pf_tile<QT, DH, DOC, false>(a, first + t, 0, smem, s_lo);
+    pf_tile<QT, DH, DOC, false, PAIR>(a, first + t, 0, smem, s_lo);
     // every wave reads s_tile after this barrier and before the next tile's first one,
     // so thread 0 rewrites it only once all have read it
     if (tid == 0) s_tile = (int)atomicAdd(ctr, 1u);
@@ -1166,22 +1163,52 @@ void launch_attend_prefill(const Shape& sh, const LayerTable& chan_map, const T*
     const bool persistent = tiles > resident;
     if (!persistent && !doc) {
       prefill_split(sh, tiles, &ad.nsplit, &ad.split_blk);
+      // Few rows: a workgroup per 32 of them whose waves cut the slots (wm_tile.hip), as long as
+      // those workgroups find a CU each, from 512 slots (shorter walks: 9 to 11 us a call
+      // either way) and, where split ranges would cut the walk further than its four waves do,
+      // up to 3072. One call of 6/3 heads of 96, ctx 1000 / 2000 / 4000 / 8000, us before ->
+      // now: 32 tokens of 8 sequences 17.8 / 21.9 / 26.4 / 30.4 (split) -> 11.6 / 16.6 / 27.0 /
+      // 46.4; of 32 sequences (192 tiles, not split) 18.0 / 29.0 / 50.8 / 96.3 -> 12.7 / 17.9 /
+      // 28.7 / 62.7. With more workgroups than CUs it is slower than the tiles (128 tokens of
+      // 32 sequences: 35 -> 51 us at ctx 2000).
+      const long kmax = (long)sh.ctx_max + sh.span();
+      const long rows32 = (long)((sh.T_new + 31) / 32) * sh.Hq * sh.B * sh.L;
+      if (rows32 <= device_cus() && kmax >= 512 && (ad.nsplit == 1 || kmax <= 3072)) {
+        launch_attend_tiles(sh, chan_map, lord, (const bf16*)Q, (const bf16*)Kc, (const bf16*)Vc,
+                            (const bf16*)Kd, (const bf16*)Vd, ctx_len, (bf16*)O, s);
+        return;
+      }
       if (ad.nsplit > 1) ad.part = (float*)scratch;
+    }
+    // Strided groups: a wave's rows see 32 gs slots more than the wave's before it, and the
+    // tile walks the last one's range, so tiles of half the queries of two heads idle less,
+    // and with the long ones first a CU pairs a long and a short one (64 sequences x 128
+    // queries of a group of 16 over 2048 slots, 6/3 heads of 96: the 256 calls of four passes
+    // over four layers 13.8 -> 11.6 ms; in tile order 13.7).
+    long wgs = tiles;
+    const bool pair = !doc && ad.nsplit == 1 && sh.gs >= 4 && sh.Hq / sh.Hkv % 2 == 0;
+    if (pair) {
+      ad.n_qtiles = (sh.T_new + BQD / 2 - 1) / (BQD / 2);
+      wgs = (long)ad.n_qtiles * sh.Hq / 2 * sh.B * sh.L;
     }
     uint32_t* queue = persistent ? (uint32_t*)scratch : nullptr;
     const AttnArgs<bf16>& ab = *reinterpret_cast<const AttnArgs<bf16>*>(&ad);
-    const dim3 gd((unsigned)(persistent ? resident : tiles * ad.nsplit)),
+    const dim3 gd((unsigned)(persistent ? resident : wgs * ad.nsplit)),
         bd(PfDma<kPfQt, 64>::NT);
     if (persistent) hipLaunchKernelGGL(queue_reset_kernel, dim3(1), dim3(kQueueWords), 0, s, queue);
     if (sh.d == 64) {
       if (doc) hipLaunchKernelGGL((attend_prefill_dma_kernel<kPfQt, 64, true>), gd, bd, 0, s, ab, queue);
       else if (ad.nsplit > 1)
         hipLaunchKernelGGL((attend_prefill_dma_kernel<kPfQt, 64, false, true>), gd, bd, 0, s, ab, queue);
+      else if (pair)
+        hipLaunchKernelGGL((attend_prefill_dma_kernel<kPfQt, 64, false, false, true>), gd, bd, 0, s, ab, queue);
       else hipLaunchKernelGGL((attend_prefill_dma_kernel<kPfQt, 64, false>), gd, bd, 0, s, ab, queue);
     } else {
       if (doc) hipLaunchKernelGGL((attend_prefill_dma_kernel<kPfQt, 96, true>), gd, bd, 0, s, ab, queue);
       else if (ad.nsplit > 1)
         hipLaunchKernelGGL((attend_prefill_dma_kernel<kPfQt, 96, false, true>), gd, bd, 0, s, ab, queue);
+      else if (pair)
+        hipLaunchKernelGGL((attend_prefill_dma_kernel<kPfQt, 96, false, false, true>), gd, bd, 0, s, ab, queue);
       else hipLaunchKernelGGL((attend_prefill_dma_kernel<kPfQt, 96, false>), gd, bd, 0, s, ab, queue);
     }
     if (ad.nsplit > 1) {

@@ -111,11 +111,6 @@ __device__ __forceinline__ void lds_dma16_stream(uint32_t lds_addr, uint32_t vof
                : "memory", "m0");
 }
 
-// vmcnt(n) for n < 64; a compiler barrier too (the copies are invisible to the compiler)
-template <int N> __device__ __forceinline__ void wait_copies() {
-  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-
 template <int DH, int NW, bool DOC, bool ONCE>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3)))
 void attend_decode_mfma_kernel(DecodeArgs<bf16> a) {

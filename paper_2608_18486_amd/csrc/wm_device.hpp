@@ -137,10 +137,15 @@ __device__ __forceinline__ void lds_dma16(uint32_t lds_addr, uint32_t voff,
                : "memory", "m0");
 }
 
-// s_waitcnt vmcnt(n) (expcnt and lgkmcnt left alone), n < 16
+// s_waitcnt vmcnt(n) (expcnt and lgkmcnt left alone), n < 64: bits 3..0 and 15..14
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 16, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | N);
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4) << 14);
+}
+
+// vmcnt(n) for n < 64; a compiler barrier too (the copies are invisible to the compiler)
+template <int N> __device__ __forceinline__ void wait_copies() {
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
 // Workgroups are dispatched round-robin over the chip's 8 XCDs (block i goes to

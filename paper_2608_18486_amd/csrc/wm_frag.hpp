@@ -67,4 +67,18 @@ __device__ __forceinline__ bf16x8 pf_ldv(const char* sm, const PfLane<DH>& lo, u
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// Sum of the 16 bf16 weights of a lane, two dot products against (1, 1) per pair of
+// fragments' halves: the normaliser then adds exactly the weights the PV products use.
+__device__ __forceinline__ float pf_wsum(const bf16x8& a, const bf16x8& b) {
+  const bf16x2 one = {(bf16)1.f, (bf16)1.f};
+  float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const bf16x2 pa = {a[2 * e], a[2 * e + 1]}, pb = {b[2 * e], b[2 * e + 1]};
+    s0 = __builtin_amdgcn_fdot2_f32_bf16(pa, one, s0, false);
+    s1 = __builtin_amdgcn_fdot2_f32_bf16(pb, one, s1, false);
+  }
+  return s0 + s1;
+}
+
 }  // namespace wm

@@ -141,6 +141,12 @@ void launch_attend_prefill(const Shape& sh, const LayerTable& chan_map, const T*
                            const int32_t* ctx_len, const int32_t* doc, T* O, void* scratch,
                            hipStream_t s);
 
+// The same for small grids without documents (bf16, head dims 64 and 96; wm_tile.hip); lord
+// holds the consumers sorted by channel.
+void launch_attend_tiles(const Shape& sh, const LayerTable& chan, const LayerTable& lord,
+                         const bf16* Q, const bf16* Kc, const bf16* Vc, const bf16* Kd,
+                         const bf16* Vd, const int32_t* ctx_len, bf16* O, hipStream_t s);
+
 // Gradients of the full-sequence channel attention (bf16, head dims 64 and 96): dQ
 // [L][B][Hq][T][d], dKc / dVc [k][B][Hkv][S_cap][d] (slots below ctx_len[b] + T written),
 // dKd / dVd [k][Hkv][d], all fp32; rows: attend_backward_rows_bytes of workspace.
