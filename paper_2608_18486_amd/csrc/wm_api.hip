@@ -582,11 +582,9 @@ void run_layer_attend(const wm_dims& d, const wm_params& P, int l, const T* H,
                              ctx_len, Q, l, 1, s);
   }
   if (!few) {
-    wm::launch_row_rms_strided<T>(H + (long)l * sh.D, sh.N(), sh.D, (long)sh.L * sh.D, sh.L,
-                                  sh.eps, rinv + l, s);
     if (!have_tab) wm::launch_rope_table(sh, ctx_len, tab, s);
     if (!q_prefolded) wm::launch_q_fold<T>(sh, (const T*)P.g_in, (const T*)P.Wq, wq, l, 1, s);
-    wm::launch_q_layers<T>(sh, H, rinv, (const T*)P.g_qnorm, tab, Q, wq, l, 1, s);
+    wm::launch_layer_queries<T>(sh, H, rinv, (const T*)P.g_qnorm, tab, Q, wq, l, s);
   }
   const wm::Shape sh1 = one_layer(sh);
   wm::LayerTable mt{};
@@ -1091,10 +1089,8 @@ void run_passes_backward(const wm_dims& d, const wm_params& P, const bf16* W_o, 
       gemm(opnd(gb, 1, D, 0, false), opnd(Ol, 1, HQ, 0, false), dW_o + (long)l * D * HQ, HQ, 1, 0,
            D, HQ, Ng, 1, true, s, 0, 0, 0, 0, (float*)at(ws, Ly.split));
       // layer l's queries again, then its attention gradients on channel c alone
-      wm::launch_row_rms_strided<bf16>(H + (long)l * D, Ng, D, (long)L * D, L, d.eps, rinv + l,
-                                       s);
-      wm::launch_q_layers<bf16>(shq, H, rinv, (const bf16*)P.g_qnorm, tab, Ql,
-                                (const bf16*)at(fw, Lf.wq), l, 1, s);
+      wm::launch_layer_queries<bf16>(shq, H, rinv, (const bf16*)P.g_qnorm, tab, Ql,
+                                     (const bf16*)at(fw, Lf.wq), l, s);
       const long dofs = ((long)c * d.Hkv) * d.d;
       wm::launch_attend_backward(sh1, m0, cg0, Ql, K + c * cslice, V + c * cslice,
                                  (const bf16*)P.Kd + dofs, (const bf16*)P.Vd + dofs, Ol, dob,

@@ -39,7 +39,18 @@ struct TabLds<Epi, std::void_t<decltype(Epi::kTabLds)>> {
   static constexpr bool value = Epi::kTabLds;
 };
 
-template <typename T, int BK_, int WGO_, int WGN_, int WO_, int WN_> struct ProjCfg {
+// Epilogues with kOwnRms scale each token by the 1/RMS of its activation row (all K of it
+// pass through the block): the DMA kernel sums the squares of the X fragments as it
+// multiplies them and hands them to row_squares() before finish().
+template <class Epi, class = void> struct OwnRms { static constexpr bool value = false; };
+template <class Epi>
+struct OwnRms<Epi, std::void_t<decltype(Epi::kOwnRms)>> {
+  static constexpr bool value = Epi::kOwnRms;
+};
+
+template <typename T, int BK_, int WGO_, int WGN_, int WO_, int WN_, int NS_ = 3>
+struct ProjCfg {
+  static constexpr int NS = NS_;                            // LDS stages (the DMA kernel)
   static constexpr int BK = BK_, WGO = WGO_, WGN = WGN_, WO = WO_, WN = WN_;
   static constexpr int NT = 64 * WGO * WGN;                 // threads
   static constexpr int OT = 32 * WO * WGO, NTOK = 32 * WN * WGN;
@@ -208,8 +219,8 @@ __global__ __launch_bounds__(C::NT) void proj_gemm_kernel(int M, int Nout, int K
 
 // bf16 variant whose K slices travel straight from memory into LDS
 // (buffer_load ... lds: each wave instruction fills 1 KB of LDS, lane l's 16 bytes
-// at 16 l), so nothing is staged in registers and the prefetch runs two slices
-// ahead through three LDS stages. A stage holds the W and X tiles as 64-byte rows
+// at 16 l), so nothing is staged in registers and the prefetch runs NS - 1 slices
+// ahead through NS LDS stages. A stage holds the W and X tiles as 64-byte rows
 // in the swizzled chunk order of ProjCfg::chunk_at; a lane of the instruction that
 // fills rows R .. R+15 fetches row R + l/4, logical chunk (l%4) ^ swizzle, so the
 // copy lands already swizzled. Loads past the matrix or past K read zeros.
@@ -217,7 +228,7 @@ __global__ __launch_bounds__(C::NT) void proj_gemm_kernel(int M, int Nout, int K
 // the compiler, seeing LDS DMA in flight, would otherwise wait for every
 // outstanding load (the prefetched slices too) before each barrier.
 template <class C> struct DmaCfg {
-  static constexpr int NS = 3;                              // LDS stages
+  static constexpr int NS = C::NS;                          // LDS stages
   static constexpr int ROWS = C::OT + C::NTOK;              // tile rows per stage
   static constexpr int NW = C::NT / 64;
   static constexpr int NI = (ROWS / 16 + NW - 1) / NW;      // 16-row instructions per wave
@@ -227,7 +238,7 @@ template <class C> struct DmaCfg {
   static constexpr int STAGE_BYTES = ROWS_PAD * 64;
   static_assert(C::SWZ && C::LDA == 32, "64-byte swizzled rows");
   static_assert(C::OT % 16 == 0 && C::NTOK % 16 == 0, "16-row instruction blocks");
-  static_assert(NI <= 15, "vmcnt encodes at most 15 here");
+  static_assert(NI * (NS - 2) < 64, "the copies in flight behind one vmcnt");
 };
 
 template <class C, typename T, class XLoad, class WLoad, class Epi>
@@ -291,6 +302,9 @@ __global__ __launch_bounds__(C::NT) void proj_gemm_dma_kernel(int M, int Nout, i
 #pragma unroll
     for (int j = 0; j < C::WN; ++j) acc[i][j] = zero16();
 
+  float ss[C::WN];  // kOwnRms: this lane's share of its tokens' sums of squares
+#pragma unroll
+  for (int j = 0; j < C::WN; ++j) ss[j] = 0.f;
   auto compute = [&](int stage) {
     const T* Ws = smem + stage * D::ROWS_PAD * 32;
     const T* Xs = Ws + C::OT * 32;
@@ -307,6 +321,12 @@ __global__ __launch_bounds__(C::NT) void proj_gemm_dma_kernel(int M, int Nout, i
       for (int i = 0; i < C::WO; ++i)
 #pragma unroll
         for (int j = 0; j < C::WN; ++j) acc[i][j] = mma32(acc[i][j], a[i], b[j]);
+      if constexpr (OwnRms<Epi>::value) {
+#pragma unroll
+        for (int j = 0; j < C::WN; ++j)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) ss[j] = fmaf((float)b[j][e], (float)b[j][e], ss[j]);
+      }
     }
   };
 
@@ -315,13 +335,13 @@ __global__ __launch_bounds__(C::NT) void proj_gemm_dma_kernel(int M, int Nout, i
   epi.template begin<C>(g, nw0, lane, est);
 
   const int kb_beg = kbeg / C::BK, kb_end = (kend + C::BK - 1) / C::BK;
-  issue(kb_beg, 0);
-  issue(kb_beg + 1, 1);
+#pragma unroll
+  for (int u = 0; u < D::NS - 1; ++u) issue(kb_beg + u, u);
   for (int kb = kb_beg, st = 0; kb < kb_end; ++kb, st = st == D::NS - 1 ? 0 : st + 1) {
-    // this wave's loads of slice kb are done once only the next slice's remain
-    wait_vmcnt<D::NI>();
+    // this wave's loads of slice kb are done once only the next NS - 2 slices' remain
+    wait_vmcnt<D::NI * (D::NS - 2)>();
     __syncthreads();  // every wave's slice kb is in LDS, and slice kb-1 is consumed
-    issue(kb + 2, st == 0 ? 2 : st - 1);  // into the stage slice kb-1 used
+    issue(kb + D::NS - 1, st == 0 ? D::NS - 1 : st - 1);  // into the stage slice kb-1 used
     compute(st);
     if ((kb + 1) % seg_len == 0 && kb + 1 < kb_end)
       epi.template segment<C>(g, (kb + 1) / seg_len, nw0, acc, lane, est);
@@ -340,6 +360,7 @@ __global__ __launch_bounds__(C::NT) void proj_gemm_dma_kernel(int M, int Nout, i
     epi.template stage_tab<C>(g, n0, (char*)smem, tid);
     __syncthreads();
   }
+  if constexpr (OwnRms<Epi>::value) epi.template row_squares<C>(g, ow0, nw0, ss, K, lane, est);
   epi.template finish<C>(g, ow0, nw0, acc, lane, est, EpiLds{(char*)smem, w, n0});
 }
 

@@ -88,6 +88,10 @@ void launch_q_project(const Shape& sh, const T* H, const float* rinv, const T* g
 template <typename T>
 void launch_q_fold(const Shape& sh, const T* g_in, const T* Wq, T* wfold, int l0, int nl,
                    hipStream_t s);
+// One layer's queries with its input norm: rinv[n][l] is written, Q receives [B][Hq][T_new][d].
+template <typename T>
+void launch_layer_queries(const Shape& sh, const T* H, float* rinv, const T* g_qnorm,
+                          const float* rope_tab, T* Q, const T* wfold, int l, hipStream_t s);
 template <typename T>
 void launch_q_layers(const Shape& sh, const T* H, const float* rinv, const T* g_qnorm,
                      const float* rope_tab, T* Q, const T* wfold, int l0, int nl, hipStream_t s);

@@ -197,7 +197,7 @@ template <int DH> __device__ __forceinline__ int rope_row_swz(int t) {
 // write (lanes without one write to a small trash area of the workspace). So each
 // wave issues a fixed sequence of memory operations, and waiting for a load leaves
 // the earlier blocks' stores in flight instead of draining them.
-//   scale_at(n) -> float   the row's 1/RMS
+//   scale_at(n, jn) -> float   the row's 1/RMS (n: the wave's 32-token block jn)
 //   aux_at(n)   -> int     a per-token value the destination needs (or 0)
 //   dst_at(n, head, aux) -> T*   the row's destination, nullptr when there is none
 //   tab, tab_n0: the RoPE table rows of tokens tab_n0 .. : with TABLDS the block's rows
@@ -232,7 +232,7 @@ __device__ __forceinline__ void head_epilogue(f32x16 (&acc)[WO][WN], int ow0, in
     const int n = nw0 + 32 * jn + r;
     in[jn] = n < M;
     nn[jn] = in[jn] ? n : M - 1;
-    sc[jn] = scale_at(nn[jn]);
+    sc[jn] = scale_at(nn[jn], jn);
     aux[jn] = aux_at(nn[jn]);
   }
   f32x4 tb[DH / 16][2];  // (cos, sin) of angle indices 8g + 4h + t, t = 0..3
@@ -413,7 +413,7 @@ template <typename T, int DH> struct KVEpi {
     head_epilogue<T, DH, C::WO, C::WN, kUsesLds, kTabLds>(
         acc, ow0, nw0, lane, M, key, g_knorm + (long)j * DH,
         kTabLds ? (const float*)(lds.p + tab_off<C>()) : tab, kTabLds ? lds.n0 : 0, eps,
-        [&](int n) { return rs[(long)g * M + n]; },
+        [&](int n, int) { return rs[(long)g * M + n]; },
         [&](int n) { return ctx_at(ctx_len, n / T_new, ctx_hi) + gq; },
         [&](int n, int head, int pos0) -> T* {
           if (head >= Hkv) return nullptr;
@@ -426,7 +426,10 @@ template <typename T, int DH> struct KVEpi {
   }
 };
 
-template <typename T, int DH> struct QEpi {
+// RMS: the input norm comes from the product's own pass over the rows (one layer a launch),
+// and the waves of the first head store it for the calls that follow (the pool's).
+template <typename T, int DH, bool RMS = false> struct QEpi {
+  static constexpr bool kOwnRms = RMS;
   static constexpr bool kUsesLds = false;
   static constexpr bool kTabLds = DH != 96;  // RoPE rows in LDS (as for the keys)
   template <class C> static constexpr size_t tab_end() {
@@ -437,23 +440,37 @@ template <typename T, int DH> struct QEpi {
   }
   T* Q;
   T* trash;  // kTrashElems elements of workspace
-  const float* rs;  // [M][L] 1 / RMS of each consumer's input state (the input RMSNorm)
+  float* rs;  // [M][L] 1 / RMS of each consumer's input state (the input RMSNorm)
   const T* g_qnorm;
   const float* tab;
   int M, T_new, B, Hq, L;
   int l0;  // group g of the launch is consumer layer l0 + g; Q holds the launch's layers
   float eps;
-  using State = NoState;
+  struct State {
+    float rinv[4];  // RMS: of this lane's tokens
+  };
+  template <class C>
+  __device__ void row_squares(int l, int ow0, int nw0, float (&ss)[C::WN], int K, int lane,
+                              State& st) const {
+    static_assert(C::WN <= 4, "the state holds every token of a lane");
+#pragma unroll
+    for (int j = 0; j < C::WN; ++j) {
+      st.rinv[j] = 1.0f / sqrtf(halves_sum(ss[j]) / (float)K + eps);
+      const int n = nw0 + 32 * j + (lane & 31);
+      if (ow0 == 0 && lane < 32 && n < M) rs[(long)n * L + l0 + l] = st.rinv[j];
+    }
+  }
   template <class C> __device__ void begin(int, int, int, State&) const {}
   template <class C>
   __device__ void segment(int, int, int, f32x16 (&)[C::WO][C::WN], int, State&) const {}
   template <class C>
   __device__ void finish(int l, int ow0, int nw0, f32x16 (&acc)[C::WO][C::WN], int lane,
-                         State&, const EpiLds& lds) const {
+                         State& st, const EpiLds& lds) const {
     head_epilogue<T, DH, C::WO, C::WN, false, kTabLds>(
         acc, ow0, nw0, lane, M, true, g_qnorm + (long)(l0 + l) * DH,
         kTabLds ? (const float*)lds.p : tab, kTabLds ? lds.n0 : 0, eps,
-        [&](int n) { return rs[(long)n * L + l0 + l]; }, [](int) { return 0; },
+        [&](int n, int jn) { return RMS ? st.rinv[jn] : rs[(long)n * L + l0 + l]; },
+        [](int) { return 0; },
         [&](int n, int head, int) -> T* {
           if (head >= Hq) return nullptr;
           const int b = n / T_new, i = n - b * T_new;
@@ -619,6 +636,19 @@ template <bool Q> struct ProjShapeD<bf16, false, 96, Q> {
   using C = ProjCfg<bf16, 32, Q ? 2 : 3, Q ? 4 : 2, 3, 2>;
 };
 template <bool Q> struct ProjShapeD<bf16, true, 96, Q> { using C = ProjCfg<bf16, 32, 3, 2, 3, 1>; };
+// One layer of one token group (the pass driver, the layer-by-layer calls): grids of the few-
+// token tiles above that leave CUs without a block (fewer than 256) take half or a third of
+// their channels per block of two waves. At 1024 tokens, D = 512, 6 heads of 96: queries 32
+// blocks 13.2 us, 96 blocks 8.4 us; output projection 64 blocks 8.4 us, 128 blocks 7.3 us. At
+// 8192 tokens the queries take 17.3 us with 256 wide blocks, 18.3 with 768 narrow ones (the
+// activations are read once per channel tile). Four stages: the short K loop (16 slices) of
+// a block that shares its CU with one other starts with three slices in flight.
+using Narrow96 = ProjCfg<bf16, 32, 1, 2, 3, 1, 4>;
+using Narrow64 = ProjCfg<bf16, 32, 1, 2, 2, 1, 4>;
+// The output projection where 128 x 128 tiles cover the CUs but 256 x 256 ones do not: the
+// activations and weights are read half as often as by 128 x 64 tiles (8192 tokens, D = 512:
+// 16.7 -> 15.3 us).
+using ResidMid = ProjCfg<bf16, 32, 2, 2, 2, 2>;
 // Router: 288 channels x 128 tokens per bf16 block on 6 waves, 96 x 64 per wave (the
 // channel count 2kL is small: 288 for L = k = 12, so a block covers all of it and the
 // stacked states are read once; measured 10% faster than 96-channel blocks at L = 24).
@@ -1258,15 +1288,14 @@ void launch_kv_project(const Shape& sh, const T* mixed, const float* rinv_mid, c
 
 // Layers l0 .. l0 + nl - 1; wfold holds the folded weights of all L layers (layer l at
 // l * Hq d * D) followed by the trash area; Q receives [nl][B][Hq][T_new][d].
-template <typename T, int DH, bool FEW>
-static void q_gemm(const Shape& sh, const T* H, const float* rinv, const T* wfold,
-                   const T* g_qnorm, const float* rope_tab, T* Q, int l0, int nl, hipStream_t s) {
-  using C = typename ProjShapeD<T, FEW, DH, true>::C;
+template <typename T, int DH, class C, bool RMS = false>
+static void q_gemm(const Shape& sh, const T* H, float* rinv, const T* wfold, const T* g_qnorm,
+                   const float* rope_tab, T* Q, int l0, int nl, hipStream_t s) {
   const int M = sh.N(), Nout = sh.Hq * DH, K = sh.D;
   PlainRows<T> x{H + (long)l0 * K, K, (long)sh.L * K, M};
   PlainRows<T> w{wfold + (long)l0 * Nout * K, (long)Nout * K, K, Nout};
   T* trash = const_cast<T*>(wfold) + (q_fold_elems(sh) - kTrashElems);
-  QEpi<T, DH> e{Q, trash, rinv, g_qnorm, rope_tab, M, sh.T_new, sh.B, sh.Hq, sh.L, l0, sh.eps};
+  QEpi<T, DH, RMS> e{Q, trash, rinv, g_qnorm, rope_tab, M, sh.T_new, sh.B, sh.Hq, sh.L, l0, sh.eps};
   launch_proj<C, T>(M, Nout, K, nl, kNoSegments, 0, x, w, e, s);
 }
 
@@ -1278,29 +1307,65 @@ void launch_q_fold(const Shape& sh, const T* g_in, const T* Wq, T* wfold, int l0
                sh.Hq * sh.d, sh.D, s);
 }
 
+// few tokens, or a grid of large tiles that would not cover the chip: small tiles
+static bool q_small_tiles(const Shape& sh, int nl, int ntok, int ot) {
+  return sh.N() <= kFewTokens ||
+         (long)nl * ((sh.N() + ntok - 1) / ntok) * ((sh.Hq * sh.d + ot - 1) / ot) < 128;
+}
+
 template <typename T>
 void launch_q_layers(const Shape& sh, const T* H, const float* rinv, const T* g_qnorm,
                      const float* rope_tab, T* Q, const T* wfold, int l0, int nl,
                      hipStream_t s) {
   const int M = sh.N();
   if (M <= 0 || nl <= 0) return;
-  // few tokens, or a grid of large tiles that would not cover the chip: small tiles
-  using CL = typename ProjShape<T, false>::C;
-  const long big = (long)nl * ((M + CL::NTOK - 1) / CL::NTOK) *
-                   ((sh.Hq * sh.d + CL::OT - 1) / CL::OT);
-  const bool few = M <= kFewTokens || big < 128;
+  const bool few = q_small_tiles(sh, nl, ProjShape<T, false>::C::NTOK, ProjShape<T, false>::C::OT);
+  float* rs = const_cast<float*>(rinv);  // read only: the norms were computed before
+#define WM_Q(DH, FEW) \
+  q_gemm<T, DH, typename ProjShapeD<T, FEW, DH, true>::C>(sh, H, rs, wfold, g_qnorm, rope_tab, Q, \
+                                                          l0, nl, s)
   if (sh.d == 96) {
     if constexpr (sizeof(T) == 2) {
-      if (few) q_gemm<T, 96, true>(sh, H, rinv, wfold, g_qnorm, rope_tab, Q, l0, nl, s);
-      else q_gemm<T, 96, false>(sh, H, rinv, wfold, g_qnorm, rope_tab, Q, l0, nl, s);
+      if (few) WM_Q(96, true);
+      else WM_Q(96, false);
     }
   } else if (sh.d == 64) {
-    if (few) q_gemm<T, 64, true>(sh, H, rinv, wfold, g_qnorm, rope_tab, Q, l0, nl, s);
-    else q_gemm<T, 64, false>(sh, H, rinv, wfold, g_qnorm, rope_tab, Q, l0, nl, s);
+    if (few) WM_Q(64, true);
+    else WM_Q(64, false);
   } else {
-    if (few) q_gemm<T, 32, true>(sh, H, rinv, wfold, g_qnorm, rope_tab, Q, l0, nl, s);
-    else q_gemm<T, 32, false>(sh, H, rinv, wfold, g_qnorm, rope_tab, Q, l0, nl, s);
+    if (few) WM_Q(32, true);
+    else WM_Q(32, false);
   }
+#undef WM_Q
+}
+
+// One layer, its input norm included. On small tiles (bf16) the product sums the squares of
+// the rows it reads anyway (a launch of its own for the norm: 3.8 us of a 52 us layer at 1024
+// tokens, 5.3 of 95 at 8192); large ones, whose blocks would each repeat the sums for their
+// channel tile, take the norms from row_rms.
+template <typename T>
+void launch_layer_queries(const Shape& sh, const T* H, float* rinv, const T* g_qnorm,
+                          const float* rope_tab, T* Q, const T* wfold, int l, hipStream_t s) {
+  if (sh.N() <= 0) return;
+  using CL = typename ProjShape<T, false>::C;
+  if constexpr (sizeof(T) == 2) {
+    if (sh.d != 32 && q_small_tiles(sh, 1, CL::NTOK, CL::OT)) {
+      using CW = typename ProjShapeD<T, true, 96, true>::C;
+      using CS = typename ProjShape<T, true>::C;
+      if (sh.d == 64 && proj_blocks<CS>(sh.N(), sh.Hq * 64, 1) < 256)
+        q_gemm<T, 64, Narrow64, true>(sh, H, rinv, wfold, g_qnorm, rope_tab, Q, l, 1, s);
+      else if (sh.d == 64)
+        q_gemm<T, 64, CS, true>(sh, H, rinv, wfold, g_qnorm, rope_tab, Q, l, 1, s);
+      else if (proj_blocks<CW>(sh.N(), sh.Hq * 96, 1) < 256)
+        q_gemm<T, 96, Narrow96, true>(sh, H, rinv, wfold, g_qnorm, rope_tab, Q, l, 1, s);
+      else
+        q_gemm<T, 96, CW, true>(sh, H, rinv, wfold, g_qnorm, rope_tab, Q, l, 1, s);
+      return;
+    }
+  }
+  launch_row_rms_strided<T>(H + (long)l * sh.D, sh.N(), sh.D, (long)sh.L * sh.D, sh.L, sh.eps,
+                            rinv + l, s);
+  launch_q_layers<T>(sh, H, rinv, g_qnorm, rope_tab, Q, wfold, l, 1, s);
 }
 
 template <typename T>
@@ -1374,7 +1439,19 @@ void launch_block_residual(int M, int D, int HD, const T* o_l, const T* W, const
   using CS = typename ProjShape<T, true>::C;
   const long big = (long)((M + CL::NTOK - 1) / CL::NTOK) * ((D + CL::OT - 1) / CL::OT);
   if (big >= 128) launch_proj<CL, T>(M, D, HD, 1, kNoSegments, 0, x, w, e, s);
-  else launch_proj<CS, T>(M, D, HD, 1, kNoSegments, 0, x, w, e, s);
+  else {
+    if constexpr (sizeof(T) == 2) {
+      if (proj_blocks<CS>(M, D, 1) < 256) {
+        launch_proj<Narrow64, T>(M, D, HD, 1, kNoSegments, 0, x, w, e, s);
+        return;
+      }
+      if (proj_blocks<ResidMid>(M, D, 1) >= 256) {
+        launch_proj<ResidMid, T>(M, D, HD, 1, kNoSegments, 0, x, w, e, s);
+        return;
+      }
+    }
+    launch_proj<CS, T>(M, D, HD, 1, kNoSegments, 0, x, w, e, s);
+  }
 }
 
 // The pass driver keeps the states of a group contiguous: Hg[q][b][m][l][e] is the state
@@ -1445,6 +1522,8 @@ void launch_group_scatter(const T* Yg, T* Y, int B, int T_len, int g, long row, 
                                      const T*, const T*, const float*, const int32_t*, T*, T*, \
                                      T*, hipStream_t, bool);                                   \
   template void launch_q_fold<T>(const Shape&, const T*, const T*, T*, int, int, hipStream_t); \
+  template void launch_layer_queries<T>(const Shape&, const T*, float*, const T*, const float*,   \
+                                        T*, const T*, int, hipStream_t);                          \
   template void launch_q_layers<T>(const Shape&, const T*, const float*, const T*,             \
                                    const float*, T*, const T*, int, int, hipStream_t);         \
   template void launch_q_project<T>(const Shape&, const T*, const float*, const T*, const T*,  \
