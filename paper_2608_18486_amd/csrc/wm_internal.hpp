@@ -226,8 +226,8 @@ struct RmsArgs {           // rows (o, i); offsets in rows of D
   int D, ninner, chunks, accumulate;
 };
 void launch_grad_rms(const RmsArgs& a, int nouter, hipStream_t s);
-// out[o][e] (+)= scale * sum_c part[(o chunks + c) n + e] (part is overwritten)
-void launch_grad_sum(float* part, int outer, int chunks, long n, float* out, float scale,
+// out[o][e] (+)= scale * sum_c part[(o chunks + c) n + e]
+void launch_grad_sum(const float* part, int outer, int chunks, long n, float* out, float scale,
                      int accumulate, hipStream_t s);
 void launch_grad_colsum(const float* x, long rows, int n, int chunks, float* part, hipStream_t s);
 void launch_grad_gather(const float* src, int k, int B, int H, int T, int S_cap, int d,
