@@ -276,6 +276,211 @@ __global__ __launch_bounds__(64 * NW) void attend_bwd_dq_kernel(BwdArgs a) {
   }
 }
 
+// ---------------------------------------- dq, LSE, D of small grids (split walk)
+// The kernel above with the slots cut between a workgroup's waves instead of the rows: 32
+// query rows per workgroup, wave w walks the 32-slot blocks w, w + NW, ... through a ring of
+// two blocks of its own in LDS (LDS-DMA; a wave waits only for its own copies), and the
+// waves' sums meet in LDS at the end. On small grids the time is the longest walk, a serial
+// chain of blocks, which is NW times shorter here; K and V are read once per 32 rows instead
+// of 256, which large grids would pay for in L2 traffic. (Smaller workgroups of the kernel
+// above leave its chain as long: 16 sequences x 256 queries of a group of 8 over 2048 slots,
+// 6/3 heads of 96: 8 / 4 / 2 waves 72 / 76 / 105 us, this kernel with two waves 56.)
+template <int DH, int NW>
+__global__ __launch_bounds__(64 * NW) void attend_bwd_dq_tile_kernel(BwdArgs a) {
+  constexpr int NKS = DH / 16, NDT = DH / 32, ROW = 2 * DH, CPR = ROW / 16, BKV = 32;
+  constexpr int BLK = BKV * ROW, NI = BLK / 1024, STAGE = 2 * BLK, RING = 2 * STAGE;
+  constexpr int OLD = DH + 4;  // row stride of the merge staging (floats)
+  static_assert((32 * OLD + 32 * 5) * 4 <= RING, "the merge staging fits a wave's ring");
+  __shared__ __align__(16) char smem[NW * RING];
+  const int tile = xcd_tile(blockIdx.x, (int)gridDim.x);
+  const int qtile = a.n_qtiles - 1 - tile % a.n_qtiles;
+  int y = tile / a.n_qtiles;
+  const int hq = y % a.Hq;
+  y /= a.Hq;
+  const int b = y % a.B, l = y / a.B;
+  const int c = a.chan.v[l], kvh = hq / (a.Hq / a.Hkv);
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pos0 = __builtin_amdgcn_readfirstlane(ctx_at(a.ctx_len, b, a.ctx_hi));
+  const int incl = a.mask_paper ? 0 : 1;
+  const int q0 = qtile * 32, qi = q0 + r;
+  const bool valid = qi < a.T;
+  const float cl2 = a.scale_log2;
+
+  const int pq = pos0 + a.gq + incl;  // position (+ incl) of query 0; query i adds gs i
+  const int kend = max(min(pq + a.gs * min(q0 + 31, a.T - 1), a.S_cap), 0);  // slots the tile may see
+  const int lim = valid ? pq + a.gs * qi : 0;  // slots < lim: this lane's row
+  const int wlim0 = pq + a.gs * q0;            // ... the tile's first row
+  const int nblk = (kend + BKV - 1) / BKV, nw = (nblk - w + NW - 1) / NW;
+  const long cbase = (((long)c * a.B + b) * a.Hkv + kvh) * (long)a.S_cap * DH;
+  const auto kv = make_view(a.Kc + cbase, (uint32_t)kend * ROW);
+  const auto vv = make_view(a.Vc + cbase, (uint32_t)kend * ROW);
+  uint32_t coff[NI];
+#pragma unroll
+  for (int n = 0; n < NI; ++n) {
+    const int ch = 64 * n + lane, row = ch / CPR;
+    coff[n] = (uint32_t)row * ROW + 16u * (uint32_t)((ch % CPR) ^ pf_swz<DH>(row));
+  }
+  char* ring = smem + w * RING;
+  const uint32_t ring_at = (uint32_t)(uintptr_t)ring;
+  // block j of this wave into stage st (past the wave's last: zeros, so that the copies in
+  // flight are the same number at every wait)
+  auto issue = [&](int j, int st) {
+    const uint32_t base = j < nw ? (uint32_t)(BKV * (w + NW * j)) * ROW : kOffOob;
+#pragma unroll
+    for (int n = 0; n < 2 * NI; ++n)
+      lds_dma16(__builtin_amdgcn_readfirstlane(ring_at + st * STAGE + 1024 * n),
+                base + coff[n % NI], n < NI ? kv : vv);
+  };
+
+  // the row's query, dO and O at this lane's columns (buffer loads: rows past T are zeros)
+  bf16x8 qf[NKS], df[NKS];
+  float dl = 0.f, sdp = 0.f, dpd = 0.f;
+  const long dofs = ((long)c * a.Hkv + kvh) * DH;
+  const uint32_t dbytes = a.mask_paper ? DH * 2u : 0u;
+  {
+    const long rowl = ((long)l * a.B + b) * a.T;  // (l, b, 0) in [L][B][T][Hq d]
+    const uint32_t ostride = (uint32_t)a.Hq * DH * 2u;
+    const auto qv = make_view(a.Q + (((long)l * a.B + b) * a.Hq + hq) * (long)a.T * DH,
+                              (uint32_t)a.T * DH * 2u);
+    const auto dv = make_view(a.dO + rowl * a.Hq * DH + (long)hq * DH, (uint32_t)a.T * ostride);
+    const auto ov = make_view(a.O + rowl * a.Hq * DH + (long)hq * DH, (uint32_t)a.T * ostride);
+    const auto kdv = make_view(a.mask_paper ? a.Kd + dofs : nullptr, dbytes);
+    const auto vdv = make_view(a.mask_paper ? a.Vd + dofs : nullptr, dbytes);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      const uint32_t col = (uint32_t)(16 * ks + 8 * h) * 2u;
+      qf[ks] = buf_frag<bf16>(qv, valid ? (uint32_t)qi * DH * 2u + col : kOffOob);
+      df[ks] = buf_frag<bf16>(dv, valid ? (uint32_t)qi * ostride + col : kOffOob);
+      const bf16x8 of = buf_frag<bf16>(ov, valid ? (uint32_t)qi * ostride + col : kOffOob);
+      const bf16x8 kd = buf_frag<bf16>(kdv, col), vd = buf_frag<bf16>(vdv, col);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        dl += (float)df[ks][e] * (float)of[e];
+        sdp += (float)qf[ks][e] * (float)kd[e];
+        dpd += (float)df[ks][e] * (float)vd[e];
+      }
+    }
+  }
+  const float delta = halves_sum(dl);
+  const float sd = halves_sum(sdp) * cl2;  // the dummy's score, log2 units
+  dpd = halves_sum(dpd);
+
+  // the online normaliser of the kernel above; the dummy starts the first wave's
+  const bool dummy = a.mask_paper && w == 0;
+  float m = dummy ? sd : kNegBig;
+  float sum = dummy && h == 0 ? 1.f : 0.f;
+  f32x16 dq[NDT];
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt) dq[dt] = zero16();
+  const PfLane<DH> lo = pf_lane<DH>(lane);
+  issue(0, 0);
+  int j = 0;
+  do {  // (a wave without a block walks one of zeros, every slot of it hidden)
+    const int st = j & 1;
+    // the stage block j-1 was read from (its reads have returned) takes block j+1
+    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+    issue(j + 1, st ^ 1);
+    wait_copies<2 * NI>();
+    const uint32_t kb = st * STAGE, vb = kb + BLK;
+    f32x16 sc = zero16(), dp = zero16();
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      sc = mma32(sc, pf_ldk<DH>(ring, lo, kb, ks), qf[ks]);
+      dp = mma32(dp, pf_ldk<DH>(ring, lo, vb, ks), df[ks]);
+    }
+    constexpr float kHidden = -__builtin_inff();
+    const int sb = BKV * (w + NW * j);  // the block's first slot
+    if (sb + BKV > wlim0 || sb + BKV > kend) {  // some row may not see all of it
+      const int thr = min(lim, kend) - sb - 4 * h;
+#pragma unroll
+      for (int q = 0; q < 16; ++q) sc[q] = 8 * (q >> 2) + (q & 3) < thr ? sc[q] : kHidden;
+    }
+    float mx = kHidden;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) mx = fmaxf(mx, sc[q]);
+    const float mn = fmaxf(m, halves_max(mx) * cl2);
+    if (__builtin_expect(__any(mn > m), 0)) {  // the maximum grew: rescale the sums
+      const float f = bwd_exp2(m - mn);
+      sum *= f;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) dq[dt] *= f;
+      m = mn;
+    }
+    bf16x8 ds[2];
+    float part = 0.f;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const float p = bwd_exp2(__builtin_fmaf(sc[q], cl2, -m));  // 0 when hidden
+      part += p;
+      ds[q >> 3][q & 7] = (bf16)(p * (dp[q] - delta));
+    }
+    sum += part;
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt)
+        dq[dt] = mma32(dq[dt], pf_ldv<DH>(ring, lo, kb, kh, dt), ds[kh]);
+  } while (++j < nw);
+  wait_copies<0>();  // no copy may land in the staging below, or after the block ends
+
+  // merge: each wave's rows [r][DH], then (m, sum) and (wave 0 is read) sd, dpd, delta per row
+  float* so = (float*)ring;
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      f32x4 v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = dq[dt][4 * g + i];
+      *(f32x4*)(so + r * OLD + 32 * dt + 8 * g + 4 * h) = v;
+    }
+  const float st_sum = halves_sum(sum);
+  if (h == 0) {
+    float* x = so + 32 * OLD + 5 * r;
+    x[0] = m;
+    x[1] = st_sum;
+    x[2] = sd;
+    x[3] = dpd;
+    x[4] = delta;
+  }
+  __syncthreads();
+  constexpr int C4 = DH / 4;
+  for (int e = tid; e < 32 * C4; e += 64 * NW) {
+    const int row = e / C4, d4 = 4 * (e - row * C4);
+    if (q0 + row >= a.T) break;  // rows only grow
+    const float* x0 = (const float*)smem + 32 * OLD + 5 * row;
+    float M = kNegBig;
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww) M = fmaxf(M, x0[ww * (RING / 4)]);
+    float ltot = 0.f, ow[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ww = 0; ww < NW; ++ww) {
+      const float al = bwd_exp2(x0[ww * (RING / 4)] - M);
+      ltot += x0[ww * (RING / 4) + 1] * al;
+      const f32x4 ov = *(const f32x4*)((const float*)(smem + ww * RING) + row * OLD + d4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ow[i] += ov[i] * al;
+    }
+    const float lse = M + __log2f(ltot), inv = 1.0f / ltot;
+    const float p_d = a.mask_paper ? bwd_exp2(x0[2] - lse) : 0.f;
+    const float ds_d = p_d * (x0[3] - x0[4]);
+    const long idx = (((long)l * a.B + b) * a.Hq + hq) * a.T + q0 + row;
+    const bf16x4 kd = bwd_ld8(make_view(a.mask_paper ? a.Kd + dofs : nullptr, dbytes),
+                              (uint32_t)d4 * 2u);
+    f32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = (ow[i] * inv + ds_d * (float)kd[i]) * a.scale;
+    *(f32x4*)(a.dQ + idx * DH + d4) = v;
+    if (d4 == 0) {
+      a.lse[idx] = lse;
+      a.dlt[idx] = x0[4];
+      a.pd[idx] = p_d;
+      a.dsd[idx] = ds_d;
+    }
+  }
+}
+
 // ------------------------------------------------------------------- dk, dv
 // Tile: 32 NW slots of one (channel, sequence, KV head), 32 per wave; the wave's K and V
 // rows stay in registers as the column operand. The tile walks every query block of 64
@@ -608,15 +813,35 @@ void launch_attend_backward(const Shape& sh, const LayerTable& chan_map,
   const dim3 ga(a.n_qtiles * sh.Hq * sh.B * sh.L), gb(a.n_stiles * sh.Hkv * sh.B * sh.k),
       gp(sh.k * sh.Hkv * a.dchunks), gs(sh.k * sh.Hkv);
   float* part = rows + 4 * nrow;
+  // Split walk: four waves while the workgroups find room at once (their rings take 96 KB at
+  // head dim 96, 64 at 64), two up to three per CU at head dim 96. Attention gradients of one
+  // call, us, before -> now: groups of 8 at 2048 slots, 6/3 heads of 96, 1 / 4 / 8 / 16
+  // sequences (48 / 192 / 384 / 768 workgroups) 107 / 113 / 115 / 128 -> 59 / 65 / 96 / 113, 32
+  // (1536) 185, with two waves 215; 12 heads of 64, 1 / 4 / 8 sequences (96 / 384 / 768)
+  // 78 / 90 / 116 -> 43 / 64 / (116); 128 tokens of 16 sequences, heads of 64 (768), 31.2, with
+  // two waves 31.6 and four 36.5.
+  const long rows32 = (long)((sh.T_new + 31) / 32) * sh.Hq * sh.B * sh.L, cus = device_cus();
+  const int dqw = rows32 <= (sh.d == 64 ? 2 : 1) * cus ? 4 : sh.d == 96 && rows32 <= 3 * cus ? 2 : 0;
+  BwdArgs at = a;
+  at.n_qtiles = (sh.T_new + 31) / 32;
+  const dim3 gt((unsigned)rows32);
   if (sh.d == 64) {
-    hipLaunchKernelGGL((attend_bwd_dq_kernel<64, kBwdQWaves>), ga, dim3(64 * kBwdQWaves), 0, s, a);
+    if (dqw == 4)
+      hipLaunchKernelGGL((attend_bwd_dq_tile_kernel<64, 4>), gt, dim3(64 * 4), 0, s, at);
+    else
+      hipLaunchKernelGGL((attend_bwd_dq_kernel<64, kBwdQWaves>), ga, dim3(64 * kBwdQWaves), 0, s, a);
     hipLaunchKernelGGL((attend_bwd_dkv_kernel<64, kBwdKWaves>), gb, dim3(64 * kBwdKWaves), 0, s,
                        a);
     hipLaunchKernelGGL(attend_bwd_dummy_part_kernel<64>, gp, dim3(4 * 64), 0, s, a, part);
     hipLaunchKernelGGL(attend_bwd_dummy_sum_kernel<64>, gs, dim3(4 * 64), 0, s, a,
                        (const float*)part);
   } else {
-    hipLaunchKernelGGL((attend_bwd_dq_kernel<96, kBwdQWaves>), ga, dim3(64 * kBwdQWaves), 0, s, a);
+    if (dqw == 4)
+      hipLaunchKernelGGL((attend_bwd_dq_tile_kernel<96, 4>), gt, dim3(64 * 4), 0, s, at);
+    else if (dqw == 2)
+      hipLaunchKernelGGL((attend_bwd_dq_tile_kernel<96, 2>), gt, dim3(64 * 2), 0, s, at);
+    else
+      hipLaunchKernelGGL((attend_bwd_dq_kernel<96, kBwdQWaves>), ga, dim3(64 * kBwdQWaves), 0, s, a);
     hipLaunchKernelGGL((attend_bwd_dkv_kernel<96, kBwdKWaves>), gb, dim3(64 * kBwdKWaves), 0, s,
                        a);
     hipLaunchKernelGGL(attend_bwd_dummy_part_kernel<96>, gp, dim3(4 * 96), 0, s, a, part);
