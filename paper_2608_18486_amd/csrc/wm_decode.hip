@@ -51,6 +51,7 @@ template <typename T> struct DecodeArgs {
   float scale_log2;
   LayerTable chan;
   ChannelGroups cg;
+  LayerTable live;  // the channels with a reader: the grid's channels
 };
 
 // Merge online-softmax state (m2, l2, o2) into (m, l, o).
@@ -120,7 +121,7 @@ void attend_decode_mfma_kernel(DecodeArgs<bf16> a) {
   int y = blockIdx.y;
   const int kvh = y % a.Hkv;
   y /= a.Hkv;
-  const int b = y % a.B, c = y / a.B;
+  const int b = y % a.B, c = a.live.v[y / a.B];
   const int off = a.cg.offsets[c], nmem = a.cg.offsets[c + 1] - off;
   const int grp = a.Hq / a.Hkv;
   const int G = nmem * grp * a.T_new, g0 = 32 * blockIdx.z;
@@ -320,9 +321,8 @@ __global__ __launch_bounds__(256) void attend_decode_kernel(DecodeArgs<T> a) {
   int y = blockIdx.y;
   const int kvh = y % a.Hkv;
   y /= a.Hkv;
-  const int b = y % a.B, c = y / a.B;
+  const int b = y % a.B, c = a.live.v[y / a.B];
   const int off = a.cg.offsets[c], nmem = a.cg.offsets[c + 1] - off;
-  if (nmem == 0) return;
   const int grp = a.Hq / a.Hkv;
   const int G = nmem * grp * a.T_new;
   // position of query i: pos0 + gs i (wave-uniform)
@@ -538,7 +538,11 @@ static void decode_dispatch(const DecodeArgs<T>& a, int G, dim3 grid, hipStream_
 // Splits of the matrix-core kernel: slots per workgroup halved (down to decode_split_len,
 // which sizes the partials' workspace) only until the grid holds this many workgroups, 2 per
 // CU: a workgroup's set-up and merge cost about as much as 300 slots (B = 8, ctx 4001:
-// 512 workgroups or more 132 us a step, 1024 or more 147, 2048 or more 167).
+// 512 workgroups or more 132 us a step, 1024 or more 147, 2048 or more 167). Only channels
+// with a reader count: layer by layer one of the k has one, and with all of them counted
+// (us a layer, query and attention) k = 12, 16 heads of 64, B 2, ctx 8191 took 89 and takes
+// 34; k = 12, 12 heads of 64, B 4, ctx 4000 86 and 30; k = 16, 6/3 heads of 96, B 8, ctx 4000
+// 54 and 30.
 constexpr long kDecodeMfmaBlocks = 512;
 // Cache bytes from which a call's slots are taken to be read from HBM. Attention alone, us,
 // plain copies / non-temporal ones: 221 MB 133 / 124 a step; at 13 MB that the next call
@@ -547,15 +551,16 @@ constexpr long kDecodeMfmaBlocks = 512;
 constexpr long kDecodeStreamBytes = 128L << 20;
 
 template <int DH>
-static void decode_mfma(DecodeArgs<bf16> a, int G, const Shape& sh, hipStream_t s) {
+static void decode_mfma(DecodeArgs<bf16> a, int G, int nlive, const Shape& sh, hipStream_t s) {
   const int z = std::max(1, (G + 31) / 32);
-  const long slices = (long)sh.k * sh.B * sh.Hkv * z, kend = (long)sh.ctx_max + sh.span();
+  const long slices = (long)nlive * sh.B * sh.Hkv * z, kend = (long)sh.ctx_max + sh.span();
   int len = kSplitMax;
   while (len > a.split_len && slices * ((kend + len - 1) / len) < kDecodeMfmaBlocks) len /= 2;
   a.split_len = len;  // at least decode_split_len, so the partials fit their workspace
   a.nsplit = std::max(1, (int)((kend + len - 1) / len));
-  const dim3 grid(a.nsplit, sh.Hkv * sh.B * sh.k, z);
-  // a cache read once by one row tile, and larger than the caches keep from call to call
+  const dim3 grid(a.nsplit, sh.Hkv * sh.B * nlive, z);
+  // a cache read once by one row tile, and larger (all channels: layer by layer, the other
+  // layers' calls read theirs in between) than the caches keep from call to call
   const bool once = z == 1 && 4L * sh.k * sh.B * sh.Hkv * kend * DH >= kDecodeStreamBytes;
   // Waves per workgroup: 2, which leaves a CU's LDS to five workgroups (three at head dim
   // 96); 1 where a workgroup's walk is at most 128 slots (four blocks); 4 at head dim 96
@@ -564,7 +569,7 @@ static void decode_mfma(DecodeArgs<bf16> a, int G, const Shape& sh, hipStream_t 
   // heads of 64: 77 / 87 / 111; ctx 4000, B 4: 172 / 126 / 133; ctx 1500, B 16, L 12: 144 /
   // 156 / 144; ctx 3000, B 24: 426 / 424 / 400; heads of 96, k = 8: ctx 1000, B 4: 19 / 16.7 /
   // 18.7; ctx 8000, B 1, k = 2: 31 / 26 / 23.6.
-  const long wgs = (long)a.nsplit * sh.k * sh.B * sh.Hkv * z, per = std::min<long>(kend, len);
+  const long wgs = a.nsplit * slices, per = std::min<long>(kend, len);
   const int waves = per <= 128 ? 1
                     : (DH == 96 ? wgs <= device_cus() : wgs > 5L * device_cus() && per >= 1024)
                         ? 4 : 2;
@@ -599,17 +604,18 @@ void launch_attend_decode(const Shape& sh, const LayerTable& chan_map, const Cha
   if (sh.N() <= 0) return;
   DecodeArgs<T> a{Q, Kc, Vc, Kd, Vd, ctx_len, doc, partials, O, sh.B, sh.T_new, sh.L, sh.Hq, sh.Hkv,
                   sh.S_cap, sh.mask_paper, decode_splits(sh), decode_split_len(sh), sh.gs, sh.gq,
-                  sh.ctx_hi, kLog2e / sqrtf((float)sh.d), chan_map, cg};
-  int maxmem = 0;
+                  sh.ctx_hi, kLog2e / sqrtf((float)sh.d), chan_map, cg, {}};
+  int maxmem = 0, nlive = 0;
   for (int c = 0; c < sh.k; ++c) {
     int n = cg.offsets[c + 1] - cg.offsets[c];
+    if (n > 0) a.live.v[nlive++] = c;
     if (n > maxmem) maxmem = n;
   }
   int G = maxmem * (sh.Hq / sh.Hkv) * sh.T_new;
-  dim3 grid(a.nsplit, sh.Hkv * sh.B * sh.k);
+  dim3 grid(a.nsplit, sh.Hkv * sh.B * nlive);
   if constexpr (sizeof(T) == 2) {  // fp32 at d = 96 is rejected by validation
-    if (sh.d == 96) decode_mfma<96>(a, G, sh, s);
-    else if (sh.d == 64) decode_mfma<64>(a, G, sh, s);
+    if (sh.d == 96) decode_mfma<96>(a, G, nlive, sh, s);
+    else if (sh.d == 64) decode_mfma<64>(a, G, nlive, sh, s);
     else decode_dispatch<T, 32>(a, G, grid, s);
   } else if (sh.d == 64)
     decode_dispatch<T, 64>(a, G, grid, s);

@@ -70,3 +70,33 @@ def test_few_token_step(wm, d, mode, B, T_new, D, p, ctx):
     _check_cache(Kg, Ko, K0, w, ctx_len.numpy(), "bf16", "K")
     _check_cache(Vg, Vo, V0, w, ctx_len.numpy(), "bf16", "V")
     check_close(O, Oo, "bf16", "few-token step %s" % mode)
+
+
+@pytest.mark.parametrize("k", [1, 12])
+@pytest.mark.parametrize("B,ctx", [(1, 8191), (2, 4000)])
+def test_one_layer_splits_its_own_channel(wm, k, B, ctx):
+    """One layer reads one channel of the cache: its slots are split for that channel's
+    workgroups alone (until there are 512 of them, at 256 slots or more each), however many channels have no reader in the call. The ranges
+    are counted by the partial states written into a workspace of all ones."""
+    L, Hq, d = 12, 16, 64
+    w = synth.small("one_layer", B=B, T_new=1, L=L, k=k, D=64, Hq=Hq, Hkv=Hq, d=d, ctx=ctx + 1,
+                    dtype="bf16", chan_map=[0] * L)
+    print("one layer of %d channels, B%d ctx%d" % (k, B, ctx), flush=True)
+    P = _dev(synth.make_params(w, _bias(w)))
+    H = synth.make_states(w).cuda()
+    Kc, Vc = synth.make_cache_device(w, fill=0.0)
+    ctx_len = torch.full((B,), ctx, dtype=torch.int32, device="cuda")
+    dims = _gdims(wm, w, ctx_max=ctx)
+    ws = torch.full((wm.workspace_size(dims, wm.OP_LAYER_ATTEND),), 255, dtype=torch.uint8,
+                    device="cuda")
+    O = torch.full((B, 1, Hq * d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wm.layer_attend(dims, P, 0, H, w.chan_map, ctx_len, Kc, Vc, O, ws=ws)
+    torch.cuda.synchronize()
+    assert torch.isfinite(O.float()).all()
+    words = int((ws.view(torch.int32) != -1).sum()) - B * Hq * d // 2  # less the queries
+    nsplit, rest = divmod(words, B * Hq * (d + 2))
+    assert rest == 0
+    length = 4096
+    while length > 256 and B * Hq * -(-(ctx + 1) // length) < 512:
+        length //= 2
+    assert nsplit == -(-(ctx + 1) // length), (nsplit, length)
