@@ -76,11 +76,14 @@ __device__ __forceinline__ void merge_state(float& m, float& l, float* o, float 
 // every NW-th 32-slot block through a ring of two blocks of its own in LDS (LDS-DMA, no
 // barrier: a wave waits only for its own copies). Measured at the two shapes above:
 // waves on a CU count for more than copies in flight per wave (three or four blocks per
-// ring, with half the waves, 4-30% slower). The weights stay as precise as the VALU
-// kernel's: scores from the unscaled bf16 queries, weights in fp32, split into bf16 hi + lo
-// parts for two PV products each (about 16 bits), the normaliser summed from the fp32 ones.
+// ring, with half the waves, 4-30% slower). The weights are the VALU kernel's: scores from the
+// unscaled bf16 queries, weights in fp32, cut into three bf16 parts (8 + 8 + 8 bits, exact)
+// for three PV products, the normaliser summed from the fp32 ones. (Two rounded parts, 16
+// bits, left 2.7e-6 of the terms' sum where two values cancel, three 5e-8; a step at 12 heads
+// of 64, k = 12, ctx 8000 99.2 us with two, 100.8 with three; at B = 8, T_new = 4, ctx 4001,
+// 6/3 heads of 96 80.7 and 80.8. The parts are truncated: rounding them takes longer, 107.7.)
 template <int DH, int NW_> struct DecMfma {
-      static constexpr int NW = NW_, NT = 64 * NW, NS = 2, BKV = 32;
+  static constexpr int NW = NW_, NT = 64 * NW, NS = 2, BKV = 32;
   static constexpr int NKS = DH / 16, NDT = DH / 32;
   static constexpr int ROW_BYTES = 2 * DH, CPR = ROW_BYTES / 16;
   static constexpr int BLK = BKV * ROW_BYTES;      // one K (or V) block of 32 slots
@@ -241,26 +244,30 @@ void attend_decode_mfma_kernel(DecodeArgs<bf16> a) {
       ps = sum16(p);
     }
     lsum += ps;
-    bf16x8 ph[2], pl[2];
+    // a weight's upper 16 bits are its first part; twice more from what is left: 24 bits
+    bf16x8 pw[3][2];
 #pragma unroll
     for (int q = 0; q < 16; q += 2) {
-      const bf16x2 hi = {(bf16)p[q], (bf16)p[q + 1]};
-      const uint32_t hb = __builtin_bit_cast(uint32_t, hi);
-      const bf16x2 lw = {(bf16)(p[q] - __uint_as_float(hb << 16)),
-                         (bf16)(p[q + 1] - __uint_as_float(hb & 0xffff0000u))};
-      ph[q >> 3][q & 7] = hi[0];
-      ph[q >> 3][(q & 7) + 1] = hi[1];
-      pl[q >> 3][q & 7] = lw[0];
-      pl[q >> 3][(q & 7) + 1] = lw[1];
+      uint32_t r0 = __float_as_uint(p[q]), r1 = __float_as_uint(p[q + 1]);
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const bf16x2 w2 = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(r1, r0, 0x07060302u));
+        pw[u][q >> 3][q & 7] = w2[0];
+        pw[u][q >> 3][(q & 7) + 1] = w2[1];
+        r0 = __float_as_uint(__uint_as_float(r0) - __uint_as_float(r0 & 0xffff0000u));
+        r1 = __float_as_uint(__uint_as_float(r1) - __uint_as_float(r1 & 0xffff0000u));
+      }
     }
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
+    for (int hf = 0; hf < 2; ++hf) {
+      bf16x8 vf[C::NDT];
 #pragma unroll
-      for (int dt = 0; dt < C::NDT; ++dt) {
-        const bf16x8 vf = pf_ldv<DH>(ring, lo, vh, hf, dt);
-        o[dt] = mma32(o[dt], vf, ph[hf]);
-        o[dt] = mma32(o[dt], vf, pl[hf]);
-      }
+      for (int dt = 0; dt < C::NDT; ++dt) vf[dt] = pf_ldv<DH>(ring, lo, vh, hf, dt);
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+#pragma unroll
+        for (int dt = 0; dt < C::NDT; ++dt) o[dt] = mma32(o[dt], vf[dt], pw[u][hf]);
+    }
     st = st + 1 == C::NS ? 0 : st + 1;
   } while (++j < nw);
   wait_copies<0>();  // no copy may land in the staging below, or after the block ends

@@ -100,3 +100,48 @@ def test_one_layer_splits_its_own_channel(wm, k, B, ctx):
     while length > 256 and B * Hq * -(-(ctx + 1) // length) < 512:
         length //= 2
     assert nsplit == -(-(ctx + 1) // length), (nsplit, length)
+
+
+@pytest.mark.parametrize("d", [64, 96])
+def test_weights_keep_fp32(wm, d):
+    """Two slots whose values nearly cancel under the weights 1 and exp(s): the output shows the
+    weights' own error. Bound: the bf16 rounding of the result, 2^-8 of it, and 2^-20 of the
+    terms' sum, what a score of at most 1 in fp32 (2^-24 for each of its few roundings) and an
+    exponential good to 2^-23 allow; weights of 16 bits are off by up to 2^-17."""
+    L, Hq = 16, 2
+    w = synth.small("cancel", B=1, T_new=1, L=L, k=1, D=64, Hq=Hq, Hkv=1, d=d, ctx=2,
+                    dtype="bf16", chan_map=[0] * L)
+    print("weights d%d" % d, flush=True)
+    P = synth.make_params(w, _bias(w))
+    Kc, Vc = synth.make_cache_cpu(w, fill=0.0)
+    gen = torch.Generator().manual_seed(5)
+    rows = L * Hq
+    Q = torch.randn(L, 1, Hq, 1, d, generator=gen).bfloat16()
+    Kc[:, :, :, 0] = 0
+    k1 = torch.randn(d, generator=gen).bfloat16()
+    # scores in (-0.65, -0.02): the query's part along the key replaced
+    q64, k64 = Q.double().reshape(rows, d), k1.double()
+    want = torch.linspace(-0.65, -0.02, rows, dtype=torch.float64)
+    q64 = q64 - (q64 @ k64)[:, None] * k64 / (k64 @ k64)
+    q64 = q64 + (want * d ** 0.5 / (k64 @ k64))[:, None] * k64
+    Q = q64.reshape(Q.shape).bfloat16()
+    p1 = torch.exp(Q.double().reshape(rows, d) @ k64 / d ** 0.5)
+    Kc[0, 0, 0, 1] = k1
+    # channel j cancels for row j mod rows: the bf16 pair of [1, 2) closest to p1 y = x
+    grid = 1 + torch.arange(128, dtype=torch.float64) / 128
+    for j in range(d):
+        off = (p1[j % rows] * grid[:, None] - grid[None, :]).abs()
+        i = int(off.argmin())
+        Vc[0, 0, 0, 0, j] = -float(grid[i % 128])
+        Vc[0, 0, 0, 1, j] = float(grid[i // 128])
+    x, y = Vc[0, 0, 0, 0].double(), Vc[0, 0, 0, 1].double()
+    ref = (x + p1[:, None] * y) / (1 + p1[:, None])
+    terms = (x.abs() + p1[:, None] * y.abs()) / (1 + p1[:, None])
+    O = torch.full((L, 1, 1, Hq * d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wm.channel_attend(_gdims(wm, w, mask_mode=1, ctx_max=1), _dev(P), Q.cuda(), w.chan_map,
+                      torch.tensor([1], dtype=torch.int32).cuda(), Kc.cuda(), Vc.cuda(), O)
+    torch.cuda.synchronize()
+    off = (O.double().cpu().reshape(rows, d) - ref).abs() - 2.0 ** -8 * ref.abs()
+    worst = float((off / terms).max())
+    print("worst %.3g of the terms" % worst)
+    assert worst <= 2.0 ** -20, worst
