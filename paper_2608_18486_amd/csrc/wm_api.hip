@@ -222,8 +222,10 @@ Layout layout(const wm_dims& dd, int op) {
     Ly.rinv = take(N * d.L * 4);
   if (op == WM_OP_ROUTER_MIX || all || pool) Ly.alpha = take(2 * N * d.k * d.L * 4);
   if (all || pool) Ly.mixed = take(2 * (size_t)d.k * N * d.D * es);
+  // the mid norms, or for few tokens the sums of squares they are made of
   if (op == WM_OP_ROUTER_MIX || op == WM_OP_KV_PROJECT || all || pool)
-    Ly.rinv_mid = take(2 * (size_t)d.k * N * 4);
+    Ly.rinv_mid = take(std::max(2 * (size_t)d.k * N * 4,
+                                all || pool ? wm::few_squares_bytes(make_shape(d)) : 0));
   if (op == WM_OP_KV_PROJECT || op == WM_OP_Q_PROJECT || all || pool || layer)
     Ly.tab = take(N * d.d * 4);
   if (all) Ly.q = take((size_t)d.L * N * d.Hq * d.d * es);
@@ -416,7 +418,7 @@ void run_kv_project(const wm_dims& d, const wm_params& P, const T* mixed, const 
   wm::Shape sh = make_shape(d);
   if constexpr (sizeof(T) == 2) {
     if (wm::few_tokens(sh)) {
-      wm::launch_few_kv(sh, mixed, (const T*)P.g_mid, (const T*)P.Wk, (const T*)P.Wv,
+      wm::launch_few_kv(sh, mixed, nullptr, (const T*)P.g_mid, (const T*)P.Wk, (const T*)P.Wv,
                         (const T*)P.g_knorm, ctx_len, Kc, Vc, s);
       return;
     }
@@ -471,13 +473,15 @@ void run_few_pool(const wm_dims& d, const wm::Shape& sh, const wm_params& P, con
                   hipStream_t s, void* const* events = nullptr) {
   float* part = (float*)at(ws, Ly.rpart);
   bf16* mixed = (bf16*)at(ws, Ly.mixed);
+  float* sq = (float*)at(ws, Ly.rinv_mid);
   wm::launch_few_router(sh, router_layers(d).v[0], H, (const bf16*)P.g_pre,
                         (const bf16*)P.W_alpha, part, s);
   if (events) (void)hipEventRecord((hipEvent_t)events[2], s);
-  wm::launch_few_mix(sh, H, (const bf16*)P.g_pre, (const bf16*)P.b_alpha, part, mixed, s);
+  wm::launch_few_mix(sh, H, (const bf16*)P.g_pre, (const bf16*)P.b_alpha, part, mixed, sq,
+                     s);
   if (events) (void)hipEventRecord((hipEvent_t)events[3], s);
-  wm::launch_few_kv(sh, mixed, (const bf16*)P.g_mid, (const bf16*)P.Wk, (const bf16*)P.Wv,
-                    (const bf16*)P.g_knorm, ctx_len, Kc, Vc, s);
+  wm::launch_few_kv(sh, mixed, sq, (const bf16*)P.g_mid, (const bf16*)P.Wk,
+                    (const bf16*)P.Wv, (const bf16*)P.g_knorm, ctx_len, Kc, Vc, s);
 }
 
 template <typename T>

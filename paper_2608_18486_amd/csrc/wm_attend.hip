@@ -123,7 +123,6 @@ __device__ __forceinline__ void st_pair_t(bf16* vt, int ld, const bf16x8& a, con
   for (int i = 0; i < 8; ++i) *(bf16x2*)(vt + i * ld) = bf16x2{a[i], b[i]};
 }
 __device__ __forceinline__ void st_pair_t(float* vt, int ld, const f32x8& a, const f32x8& b) {
-  typedef __attribute__((ext_vector_type(2))) float f32x2;
 #pragma unroll
   for (int i = 0; i < 8; ++i) *(f32x2*)(vt + i * ld) = f32x2{a[i], b[i]};
 }

@@ -33,15 +33,17 @@ template <int NDT> struct FewTile {
 
 // acc[dt] += W (x g)^T over the columns [k0, k1) (k0 a multiple of 16), and the sum of
 // squares of the tokens over them. Lane (h, r) of the operands: weight row 32 dt + r, token
-// r. wv, xv: views whose row t starts at byte t wrow / xoff(t); gain: the D gains.
+// r. wv, xv: views whose row t starts at byte t wrow / xoff(t); gain: the D gains; sq: this
+// lane's token's sums of squares of every eight columns, or null (then taken from x).
 template <int NDT, class XOff>
 __device__ __forceinline__ float few_product(__amdgpu_buffer_rsrc_t wv, uint32_t wrow, int wlast,
                                              __amdgpu_buffer_rsrc_t xv, XOff xoff,
-                                             const bf16* __restrict__ gain, int k0, int k1,
+                                             const bf16* __restrict__ gain,
+                                             const float* __restrict__ sq, int k0, int k1,
                                              f32x16 (&acc)[NDT], char* area, int lane) {
   using F = FewTile<NDT>;
   const int h = lane >> 5, r = lane & 31;
-  float ss = 0.f;
+  float ss = 0.f, sg = 0.f;
   const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)area);
   for (int kb = k0; kb < k1; kb += 16 * kFewBatch) {
 #pragma unroll
@@ -56,6 +58,15 @@ __device__ __forceinline__ float few_product(__amdgpu_buffer_rsrc_t wv, uint32_t
 #pragma unroll
     for (int i = 0; i < kFewBatch; ++i)  // past the range: read again, times zeros
       gf[i] = ld_frag<bf16>(gain + min(kb + 16 * i, k1 - 16) + 8 * h);
+    if (sq) {
+      f32x2 v[kFewBatch / 2];  // half h: its half of the batch's k16 steps, two sums each
+#pragma unroll
+      for (int i = 0; i < kFewBatch / 2; ++i)
+        v[i] = *(const f32x2*)(sq + min(kb + 16 * (kFewBatch / 2 * h + i), k1 - 16) / 8);
+#pragma unroll
+      for (int i = 0; i < kFewBatch / 2; ++i)
+        sg += kb + 16 * (kFewBatch / 2 * h + i) < k1 ? v[i][0] + v[i][1] : 0.f;
+    }
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
 #pragma unroll
     for (int i = 0; i < kFewBatch; ++i) {
@@ -74,7 +85,7 @@ __device__ __forceinline__ float few_product(__amdgpu_buffer_rsrc_t wv, uint32_t
     }
     asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the area takes the next batch
   }
-  return halves_sum(ss);
+  return halves_sum(sq ? sg : ss);
 }
 
 struct FewProj {
@@ -83,6 +94,7 @@ struct FewProj {
   const bf16 *W0, *W1;   // groups [0, split) from W0, the rest from W1, [H DH][D] each
   int split;
   const bf16* gain;      // [groups][D] the gain of the tokens' RMSNorm
+  const float* sq;       // [groups][M][D / 8] the tokens' sums of squares, or null
   const bf16* hgain;     // [split][DH] the head norm's gain (groups below split)
   int M, D, H, T_new, B, gs, gq;
   const int32_t* ctx_len;
@@ -134,7 +146,9 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_proj_kernel(FewProj a) {
   const float ss = few_product<NDT>(
       wv, (uint32_t)a.D * 2, DH - 1, xv,
       [&](int x) { return (uint32_t)(min(n0 + x, a.M - 1) * a.xn * 2); },
-      a.gain + (long)g * a.D, w * per, min(a.D, (w + 1) * per), acc, area[w], lane);
+      a.gain + (long)g * a.D,
+      KV && a.sq ? a.sq + ((long)g * a.M + min(n0 + r, a.M - 1)) * (a.D / 8) : nullptr, w * per,
+      min(a.D, (w + 1) * per), acc, area[w], lane);
   float* red = (float*)area[w];  // [32 tokens][LD]
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt)
@@ -226,7 +240,7 @@ void launch_few_queries(const Shape& sh, const bf16* H, const bf16* g_in, const 
                         hipStream_t s) {
   const long D = sh.D, per = (long)sh.Hq * sh.d * D;
   FewProj a{H + l0 * D, D, (long)sh.L * D, Wq + l0 * per, nullptr, nl, g_in + l0 * D,
-            g_qnorm + (long)l0 * sh.d, sh.N(), sh.D, sh.Hq, sh.T_new, sh.B, sh.gs, sh.gq,
+            nullptr, g_qnorm + (long)l0 * sh.d, sh.N(), sh.D, sh.Hq, sh.T_new, sh.B, sh.gs, sh.gq,
             ctx_len, sh.ctx_hi, sh.eps, {}, Q, nullptr, 0};
   few_proj<false>(a, sh, nl, s);
 }
@@ -254,7 +268,8 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_router_kernel(
   const float ss = few_product<1>(
       wv, (uint32_t)(K * 2), rows - 1, xv,
       [&](int x) { return (uint32_t)min(n0 + x, M - 1) * (uint32_t)(L * D * 2); },
-      g_pre + ((long)br * L + lay) * D, w * per, min(D, (w + 1) * per), acc, area[w], lane);
+      g_pre + ((long)br * L + lay) * D, nullptr, w * per, min(D, (w + 1) * per), acc, area[w],
+      lane);
   float* red = (float*)area[w];  // [32 tokens][LD]
 #pragma unroll
   for (int q4 = 0; q4 < 4; ++q4) {
@@ -286,14 +301,16 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_router_kernel(
 // ---------------------------------------------------------------------- mix
 // One token and a slice of the columns: the logits (the sources' partial sums in order, plus
 // the bias), the weights (mask, softmax), their products with 1 / RMS of the states, and the
-// mixed channels of both branches, all in fp32. A thread makes kFewJc channels of 8 columns.
+// mixed channels of both branches, all in fp32, and for the mid norm the sums of squares of
+// every eight columns before their rounding to bf16 (as the many-token mix takes them; 0.3 to
+// 1.2 us a pool more than the sums of the rounded ones, mostly at 32 tokens). A thread makes kFewJc channels of 8 columns.
 constexpr int kFewJc = 4;
 
 __global__ __launch_bounds__(256) void few_mix_kernel(const bf16* H, const bf16* g_pre,
                                                       const float* part, const bf16* bias, int M,
                                                       int L, int k, int D, int sources,
                                                       int softmax, int nofb, float eps,
-                                                      int cols, bf16* mixed) {
+                                                      int cols, bf16* mixed, float* sq) {
   extern __shared__ __align__(16) float sm[];
   const int kL = k * L, n = blockIdx.x, c0 = blockIdx.y * cols;
   float* coef = sm;           // [2][k][L]
@@ -395,14 +412,25 @@ __global__ __launch_bounds__(256) void few_mix_kernel(const bf16* H, const bf16*
       }
     }
 #pragma unroll
-    for (int jj = 0; jj < kFewJc; ++jj)
-      if (j0 + jj < k) store8(mixed + (((long)br * k + j0 + jj) * M + n) * D + e, acc[jj]);
+    for (int jj = 0; jj < kFewJc; ++jj) {
+      if (j0 + jj >= k) break;
+      const long row = ((long)br * k + j0 + jj) * M + n;
+      store8(mixed + row * D + e, acc[jj]);
+      float ss = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) ss += acc[jj][i] * acc[jj][i];
+      sq[row * (D / 8) + e / 8] = ss;
+    }
   }
 }
 
 size_t few_router_bytes(const Shape& sh) {
   return few_tokens(sh) && sh.router_mode != 1
              ? (size_t)sh.Lp * sh.N() * 2 * sh.k * sh.L * sizeof(float) : 0;
+}
+
+size_t few_squares_bytes(const Shape& sh) {
+  return few_tokens(sh) ? 2ul * sh.k * sh.N() * (sh.D / 8) * sizeof(float) : 0;
 }
 
 void launch_few_router(const Shape& sh, int s0, const bf16* H, const bf16* g_pre,
@@ -415,7 +443,7 @@ void launch_few_router(const Shape& sh, int s0, const bf16* H, const bf16* g_pre
 }
 
 void launch_few_mix(const Shape& sh, const bf16* H, const bf16* g_pre, const bf16* b_alpha,
-                    const float* part, bf16* mixed, hipStream_t s) {
+                    const float* part, bf16* mixed, float* sq, hipStream_t s) {
   // columns per workgroup: 128 or more, fewer workgroups per token as the tokens grow (each
   // sums the logits and the norms of its token again)
   const int parts = std::max(1, std::min(sh.D / 128, 128 / sh.N()));
@@ -424,14 +452,14 @@ void launch_few_mix(const Shape& sh, const bf16* H, const bf16* g_pre, const bf1
   hipLaunchKernelGGL(few_mix_kernel, dim3(sh.N(), (sh.D + cols - 1) / cols), dim3(256), lds, s, H,
                      g_pre, part, b_alpha, sh.N(), sh.L, sh.k, sh.D,
                      sh.router_mode == 1 ? 0 : sh.Lp, sh.mix_softmax,
-                     sh.router_mode == 2 ? 1 : 0, sh.eps, cols, mixed);
+                     sh.router_mode == 2 ? 1 : 0, sh.eps, cols, mixed, sq);
 }
 
-void launch_few_kv(const Shape& sh, const bf16* mixed, const bf16* g_mid, const bf16* Wk,
-                   const bf16* Wv, const bf16* g_knorm, const int32_t* ctx_len, bf16* Kc,
+void launch_few_kv(const Shape& sh, const bf16* mixed, const float* sq, const bf16* g_mid,
+                   const bf16* Wk, const bf16* Wv, const bf16* g_knorm, const int32_t* ctx_len, bf16* Kc,
                    bf16* Vc, hipStream_t s) {
   const long D = sh.D;
-  FewProj a{mixed, (long)sh.N() * D, D, Wk, Wv, sh.k, g_mid, g_knorm, sh.N(), sh.D, sh.Hkv,
+  FewProj a{mixed, (long)sh.N() * D, D, Wk, Wv, sh.k, g_mid, sq, g_knorm, sh.N(), sh.D, sh.Hkv,
             sh.T_new, sh.B, sh.gs, sh.gq, ctx_len, sh.ctx_hi, sh.eps, {}, Kc, Vc, sh.S_cap};
   few_proj<true>(a, sh, 2 * sh.k, s);
 }

@@ -103,12 +103,15 @@ void launch_q_layers(const Shape& sh, const T* H, const float* rinv, const T* g_
 constexpr int kFewRows = 32;
 bool few_tokens(const Shape& sh);
 size_t few_router_bytes(const Shape& sh);
+// The mix also writes its channels' fp32 sums of squares (few_squares_bytes) for the mid norm;
+// without them (sq null) launch_few_kv takes the norm from the bf16 channels.
+size_t few_squares_bytes(const Shape& sh);
 void launch_few_router(const Shape& sh, int s0, const bf16* H, const bf16* g_pre,
                        const bf16* W_alpha, float* part, hipStream_t s);
 void launch_few_mix(const Shape& sh, const bf16* H, const bf16* g_pre, const bf16* b_alpha,
-                    const float* part, bf16* mixed, hipStream_t s);
-void launch_few_kv(const Shape& sh, const bf16* mixed, const bf16* g_mid, const bf16* Wk,
-                   const bf16* Wv, const bf16* g_knorm, const int32_t* ctx_len, bf16* Kc,
+                    const float* part, bf16* mixed, float* sq, hipStream_t s);
+void launch_few_kv(const Shape& sh, const bf16* mixed, const float* sq, const bf16* g_mid,
+                   const bf16* Wk, const bf16* Wv, const bf16* g_knorm, const int32_t* ctx_len, bf16* Kc,
                    bf16* Vc, hipStream_t s);
 void launch_few_queries(const Shape& sh, const bf16* H, const bf16* g_in, const bf16* Wq,
                         const bf16* g_qnorm, const int32_t* ctx_len, bf16* Q, int l0, int nl,

@@ -145,3 +145,31 @@ def test_weights_keep_fp32(wm, d):
     worst = float((off / terms).max())
     print("worst %.3g of the terms" % worst)
     assert worst <= 2.0 ** -20, worst
+
+
+@pytest.mark.parametrize("d", [64, 96])
+@pytest.mark.parametrize("D", [64, 544])
+def test_few_token_mid_norm_is_the_many_token_one(wm, d, D):
+    """The mid norm's sum of squares is that of the fp32 mixed channels, as with many tokens,
+    not of their bf16 copies. Every mixed element is +-(1 + 11/128)(1 + 6/128), which bf16
+    rounds up by 3.3e-3: the value rows of 8 tokens and of the same tokens among 40 have the
+    same norm to the rounding of their elements, 2^-8 / sqrt(the elements), not 3.3e-3 apart."""
+    rows = {}
+    for B in (8, 40):
+        w = synth.small("mid_norm", B=B, T_new=1, L=1, k=1, D=D, Hq=2, Hkv=2, d=d, ctx=1,
+                        dtype="bf16", chan_map=[0])
+        print("mid norm d%d D%d N%d" % (d, D, B), flush=True)
+        P = synth.make_params(w, torch.ones(1))
+        P["b_alpha"] = torch.full_like(P["b_alpha"], 1 + 11 / 128)
+        P["g_pre"] = torch.full_like(P["g_pre"], 1 + 6 / 128)
+        gen = torch.Generator().manual_seed(3)
+        H = torch.randint(0, 2, (8, 1, 1, D), generator=gen).bfloat16() * 2 - 1
+        H = H.repeat(B // 8, 1, 1, 1)
+        Kc, Vc = synth.make_cache_cpu(w, fill=0.0)
+        Kg, Vg = Kc.cuda(), Vc.cuda()
+        wm.pool(_gdims(wm, w, router_mode=1, ctx_max=0), _dev(P), H.cuda(),
+                torch.zeros(B, dtype=torch.int32, device="cuda"), Kg, Vg)
+        torch.cuda.synchronize()
+        rows[B] = Vg[0, :8, :, 0].double().cpu()
+    ratio = float(rows[8].norm() / rows[40].norm())
+    assert abs(ratio - 1) <= 2 ** -8 / rows[8].numel() ** 0.5, ratio
