@@ -1282,13 +1282,20 @@ void launch_kv_project(const Shape& sh, const T* mixed, const float* rinv_mid, c
   const int M = sh.N();
   if (M <= 0) return;
   if (!prefolded) launch_kv_fold<T>(sh, g_mid, Wk, Wv, wfold, s);
-  // few tokens, or (bf16) a grid of the larger tiles that leaves half the CUs without a block
-  // (1024 tokens, k = 8, D = 512, 3 heads of 96: 19.6 -> 15.3 us)
+  // few tokens, or (bf16) a grid of the larger tiles that leaves half the CUs without a block:
+  // 1024 tokens, k = 8, D = 512, 3 heads of 96 (128 blocks) 19.6 -> 15.3 us. At head dim 64 the
+  // smaller tiles (128 x 64) re-read the operands four times as often as the larger (256 x 256),
+  // and from D = 1536 that outweighs the idle CUs past 96 blocks; wm_kv_project, us, larger ->
+  // smaller tiles, 96 / 112 / 128 blocks: D 512 35 -> 28 / 36 -> 32 / 37 -> 33, D 1024 48 -> 40
+  // / 49 -> 46 / 49 -> 47, D 1536 62 -> 54 / 64 -> 64 / 65 -> 67, D 2048 72 -> 62 / 75 -> 74 /
+  // 76 -> 79, D 4096 120 -> 108 / 123 -> 130 / 126 -> 140. At head dim 96 128 blocks gain at
+  // every D (D 512 32 -> 27, D 4096 109 -> 92).
   using CF = typename ProjShapeD<bf16, false, 96, false>::C;
   using CL = typename ProjShape<bf16, false>::C;
   const unsigned big = sh.d == 96 ? proj_blocks<CF>(M, sh.Hkv * 96, 2 * sh.k)
                                   : proj_blocks<CL>(M, sh.Hkv * sh.d, 2 * sh.k);
-  const bool few = M <= kFewTokens || (sizeof(T) == 2 && big <= 128);
+  const unsigned most = sh.d == 96 || sh.D < 1536 ? 128 : 96;
+  const bool few = M <= kFewTokens || (sizeof(T) == 2 && big <= most);
   if (sh.d == 96) {
     if constexpr (sizeof(T) == 2) {  // fp32 at d = 96 is rejected by validation
       if (few) kv_gemm<T, 96, true>(sh, mixed, rinv_mid, wfold, g_knorm, rope_tab, ctx_len, Kc, Vc, s);
