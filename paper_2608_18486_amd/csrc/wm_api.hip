@@ -619,11 +619,15 @@ void run_passes(const wm_dims& d, const wm_params& P, const T* W_o, const T* X,
   T* topg = (T*)at(ws, Ly.topg);
   T* Ol = (T*)at(ws, Ly.ol);
   const long gsz = (long)d.B * Tg * L * D;  // one group's states
-  wm::launch_router_fold<T>(sh0, router_layers(d), (const T*)P.g_pre, (const T*)P.W_alpha,
-                            (T*)at(ws, Ly.wa), s);
-  wm::launch_kv_fold<T>(sh0, (const T*)P.g_mid, (const T*)P.Wk, (const T*)P.Wv,
-                        (T*)at(ws, Ly.wkv), s);
-  wm::launch_q_fold<T>(sh0, (const T*)P.g_in, (const T*)P.Wq, (T*)at(ws, Ly.wq), 0, L, s);
+  // groups of few bf16 tokens read the weights as given and make their own angles
+  const bool few = sizeof(T) == 2 && wm::few_tokens(sh0);
+  if (!few) {
+    wm::launch_router_fold<T>(sh0, router_layers(d), (const T*)P.g_pre, (const T*)P.W_alpha,
+                              (T*)at(ws, Ly.wa), s);
+    wm::launch_kv_fold<T>(sh0, (const T*)P.g_mid, (const T*)P.Wk, (const T*)P.Wv,
+                          (T*)at(ws, Ly.wkv), s);
+    wm::launch_q_fold<T>(sh0, (const T*)P.g_in, (const T*)P.Wq, (T*)at(ws, Ly.wq), 0, L, s);
+  }
   wm::launch_group_gather<T>(X, Hg, d.B, d.T_new, g, L, D, s);
   for (int q = 0; q < g; ++q)
     run_pool<T>(group_dims(d, q), P, Hg + q * gsz, nullptr, Kc, Vc, Ly, ws, s, false, false,
@@ -632,7 +636,7 @@ void run_passes(const wm_dims& d, const wm_params& P, const T* W_o, const T* X,
     for (int q = 0; q < g; ++q) {
       const wm_dims dq = group_dims(d, q);
       T* Hq = Hg + q * gsz;
-      wm::launch_rope_table(make_shape(dq), nullptr, (float*)at(ws, Ly.tab), s);
+      if (!few) wm::launch_rope_table(make_shape(dq), nullptr, (float*)at(ws, Ly.tab), s);
       for (int l = 0; l < L; ++l) {
         run_layer_attend<T>(dq, P, l, Hq, chan_map, nullptr, Kc, Vc, Ol, Ly, ws, s, true, true);
         const bool last = l + 1 == L;
@@ -998,10 +1002,15 @@ void run_passes_backward(const wm_dims& d, const wm_params& P, const bf16* W_o, 
   auto Uv = [&](int j) { return (bf16*)at(ws, Ly.undo + Ly.slots * (2 * j + 1)); };
   auto Os = [&](int j) { return (bf16*)at(ws, Ly.op + Ly.outs * j); };
   const wm::Shape sh0 = make_shape(group_dims(d, 0));
-  wm::launch_router_fold<bf16>(sh0, router_layers(d), (const bf16*)P.g_pre,
-                               (const bf16*)P.W_alpha, (bf16*)at(fw, Lf.wa), s);
-  wm::launch_kv_fold<bf16>(sh0, (const bf16*)P.g_mid, (const bf16*)P.Wk, (const bf16*)P.Wv,
-                           (bf16*)at(fw, Lf.wkv), s);
+  // the forward of groups of few tokens reads the weights as given and makes its own angles;
+  // the backward recomputes its queries from the folded ones
+  const bool few = wm::few_tokens(sh0);
+  if (!few) {
+    wm::launch_router_fold<bf16>(sh0, router_layers(d), (const bf16*)P.g_pre,
+                                 (const bf16*)P.W_alpha, (bf16*)at(fw, Lf.wa), s);
+    wm::launch_kv_fold<bf16>(sh0, (const bf16*)P.g_mid, (const bf16*)P.Wk, (const bf16*)P.Wv,
+                             (bf16*)at(fw, Lf.wkv), s);
+  }
   wm::launch_q_fold<bf16>(sh0, (const bf16*)P.g_in, (const bf16*)P.Wq, (bf16*)at(fw, Lf.wq), 0,
                           L, s);
   // H^(0) = X in every layer, group by group; the initial pool
@@ -1014,7 +1023,7 @@ void run_passes_backward(const wm_dims& d, const wm_params& P, const bf16* W_o, 
   // then its pool unless it is the last step (whose pool nothing reads)
   auto step = [&](int q, bf16* Hq, bf16* O, bf16* uk, bf16* uv, bool pool) {
     const wm_dims dq = group_dims(d, q);
-    wm::launch_rope_table(make_shape(dq), nullptr, tab, s);
+    if (!few) wm::launch_rope_table(make_shape(dq), nullptr, tab, s);
     for (int l = 0; l < L; ++l) {
       bf16* Ol = O ? O + (long)l * Ng * HQ : (bf16*)at(fw, Lf.ol);
       run_layer_attend<bf16>(dq, P, l, Hq, chan_map, nullptr, K, V, Ol, Lf, fw, s, true, true);

@@ -19,6 +19,7 @@
 namespace wm {
 
 constexpr int kFewWaves = 4, kFewBatch = 8;
+static_assert(kFewRows == 32, "one tile of tokens");
 
 // A wave's share of a product of 32 NDT weight rows with 32 tokens. Its rows' next 128
 // columns (weights, then tokens; 256-byte pieces, four rows per instruction) are copied into
@@ -106,7 +107,7 @@ struct FewProj {
   int S_cap;
 };
 
-// One head of one projection for 32 tokens: grid (heads, groups, token tiles). KV: keys
+// One head of one projection for the call's tokens: grid (heads, groups). KV: keys
 // (norm, rotation) and values (neither) into the caches; else queries.
 template <int DH, bool KV>
 __global__ __launch_bounds__(64 * kFewWaves) void few_proj_kernel(FewProj a) {
@@ -116,12 +117,12 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_proj_kernel(FewProj a) {
   __shared__ __align__(16) char area[kFewWaves][F::BYTES];
   __shared__ float ssq[kFewWaves][32];
   __shared__ double freq[DH / 2];
-  const int head = blockIdx.x, g = blockIdx.y, n0 = 32 * blockIdx.z;
+  const int head = blockIdx.x, g = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool rotate = !KV || g < a.split;
-  // the epilogue's thread: token t, rotation pairs m0 .. m0 + PP - 1 (m and m + DH / 2)
-  const int t = tid >> 3, m0 = (tid & 7) * PP, n = n0 + t;
+  // the epilogue's thread: token n, rotation pairs m0 .. m0 + PP - 1 (m and m + DH / 2)
+  const int n = tid >> 3, m0 = (tid & 7) * PP;
   const int nn = min(n, a.M - 1), b = nn / a.T_new, ti = nn - b * a.T_new;
   const long pos = (long)ctx_at(a.ctx_len, b, a.ctx_hi) + a.gq + (long)a.gs * ti;
   bf16 hg[2][PP];
@@ -145,9 +146,9 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_proj_kernel(FewProj a) {
   for (int dt = 0; dt < NDT; ++dt) acc[dt] = zero16();
   const float ss = few_product<NDT>(
       wv, (uint32_t)a.D * 2, DH - 1, xv,
-      [&](int x) { return (uint32_t)(min(n0 + x, a.M - 1) * a.xn * 2); },
+      [&](int x) { return (uint32_t)(min(x, a.M - 1) * a.xn * 2); },
       a.gain + (long)g * a.D,
-      KV && a.sq ? a.sq + ((long)g * a.M + min(n0 + r, a.M - 1)) * (a.D / 8) : nullptr, w * per,
+      KV && a.sq ? a.sq + ((long)g * a.M + min(r, a.M - 1)) * (a.D / 8) : nullptr, w * per,
       min(a.D, (w + 1) * per), acc, area[w], lane);
   float* red = (float*)area[w];  // [32 tokens][LD]
 #pragma unroll
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_proj_kernel(FewProj a) {
   __syncthreads();
   float v1[PP], v2[PP], sq = 0.f;
 #pragma unroll
-  for (int ww = 0; ww < kFewWaves; ++ww) sq += ssq[ww][t];
+  for (int ww = 0; ww < kFewWaves; ++ww) sq += ssq[ww][n];
   const float rinv = 1.0f / sqrtf(sq / (float)a.D + a.eps);
   float hs = 0.f;
 #pragma unroll
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_proj_kernel(FewProj a) {
     v1[i] = v2[i] = 0.f;
 #pragma unroll
     for (int ww = 0; ww < kFewWaves; ++ww) {
-      const float* rw = (const float*)area[ww] + t * LD + m0 + i;
+      const float* rw = (const float*)area[ww] + n * LD + m0 + i;
       v1[i] += rw[0];
       v2[i] += rw[DH / 2];
     }
@@ -230,7 +231,7 @@ template <bool KV> static void few_proj(FewProj& a, const Shape& sh, int groups,
     dim = d;
   }
   std::copy(freq, freq + d / 2, a.freq);
-  const dim3 grid(a.H, groups, (a.M + 31) / 32), blk(64 * kFewWaves);
+  const dim3 grid(a.H, groups), blk(64 * kFewWaves);
   if (d == 96) hipLaunchKernelGGL((few_proj_kernel<96, KV>), grid, blk, 0, s, a);
   else hipLaunchKernelGGL((few_proj_kernel<64, KV>), grid, blk, 0, s, a);
 }
@@ -247,7 +248,7 @@ void launch_few_queries(const Shape& sh, const bf16* H, const bf16* g_in, const 
 
 // ------------------------------------------------------------------- router
 // part[m][n][br kL + o] = (W_alpha[br][o][m] . (g_pre x)) / RMS(x) for stacked source m (layer
-// s0 + p m): grid (row tiles of 32 per branch, sources, branches x token tiles).
+// s0 + p m): grid (row tiles of 32 per branch, sources, branches).
 __global__ __launch_bounds__(64 * kFewWaves) void few_router_kernel(
     const bf16* H, const bf16* W, const bf16* g_pre, int M, int L, int Lp, int D, int kL, int s0,
     int p, int nofb, float eps, float* part) {
@@ -255,8 +256,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_router_kernel(
   constexpr int LD = 36;
   __shared__ __align__(16) char area[kFewWaves][F::BYTES];
   __shared__ float ssq[kFewWaves][32];
-  const int o0 = 32 * blockIdx.x, m = blockIdx.y, br = blockIdx.z & 1;
-  const int n0 = 32 * (blockIdx.z >> 1), lay = s0 + p * m;
+  const int o0 = 32 * blockIdx.x, m = blockIdx.y, br = blockIdx.z, lay = s0 + p * m;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, r = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const long K = (long)Lp * D;
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_router_kernel(
   f32x16 acc[1] = {zero16()};
   const float ss = few_product<1>(
       wv, (uint32_t)(K * 2), rows - 1, xv,
-      [&](int x) { return (uint32_t)min(n0 + x, M - 1) * (uint32_t)(L * D * 2); },
+      [&](int x) { return (uint32_t)min(x, M - 1) * (uint32_t)(L * D * 2); },
       g_pre + ((long)br * L + lay) * D, nullptr, w * per, min(D, (w + 1) * per), acc, area[w],
       lane);
   float* red = (float*)area[w];  // [32 tokens][LD]
@@ -280,11 +280,11 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_router_kernel(
   }
   if (h == 0) ssq[w][r] = ss;
   __syncthreads();
-  const int t = tid >> 3, c = 4 * (tid & 7), n = n0 + t;
+  const int n = tid >> 3, c = 4 * (tid & 7);
   if (n >= M) return;
   float sq = 0.f;
 #pragma unroll
-  for (int ww = 0; ww < kFewWaves; ++ww) sq += ssq[ww][t];
+  for (int ww = 0; ww < kFewWaves; ++ww) sq += ssq[ww][n];
   const float rinv = 1.0f / sqrtf(sq / (float)D + eps);
   float* dst = part + ((long)m * M + n) * 2 * kL + (long)br * kL;
 #pragma unroll
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_router_kernel(
     const int o = o0 + c + i;
     float v = 0.f;
 #pragma unroll
-    for (int ww = 0; ww < kFewWaves; ++ww) v += ((const float*)area[ww])[t * LD + c + i];
+    for (int ww = 0; ww < kFewWaves; ++ww) v += ((const float*)area[ww])[n * LD + c + i];
     // without feedback channel o / L reads only the sources of layers <= o / L
     if (o < kL) dst[o] = nofb && lay > o / L ? 0.f : v * rinv;
   }
@@ -437,7 +437,7 @@ void launch_few_router(const Shape& sh, int s0, const bf16* H, const bf16* g_pre
                        const bf16* W_alpha, float* part, hipStream_t s) {
   if (sh.router_mode == 1) return;  // static weights: no router
   const int kL = sh.k * sh.L, M = sh.N();
-  hipLaunchKernelGGL(few_router_kernel, dim3((kL + 31) / 32, sh.Lp, 2 * ((M + 31) / 32)),
+  hipLaunchKernelGGL(few_router_kernel, dim3((kL + 31) / 32, sh.Lp, 2),
                      dim3(64 * kFewWaves), 0, s, H, W_alpha, g_pre, M, sh.L, sh.Lp, sh.D, kL, s0,
                      sh.p, sh.router_mode == 2 ? 1 : 0, sh.eps, part);
 }

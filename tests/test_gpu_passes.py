@@ -265,3 +265,37 @@ def test_prefill_passes_paper_shape(wm, mix_mode, passes):
                      kap[br].max()))
             check_close(G[:, b:b + 1], Ref, w.dtype, "paper g8 mix%d %s b=%d"
                         % (mix_mode, "KV"[br], b), slack=np.broadcast_to(slack, Ref.shape))
+
+
+@pytest.mark.parametrize("backward", [False, True])
+def test_few_token_groups_leave_out_the_folds(wm, backward):
+    """Groups of at most 32 bf16 tokens read the weights as given: the folded router and K/V
+    weights (and, where no gradient recomputes the queries, the folded query weights) are not
+    made, so that much of a workspace of all ones stays as it was."""
+    w = synth.small("few_groups", B=2, T_new=64, L=5, k=3, D=256, Hq=4, Hkv=2, d=64, ctx=0,
+                    dtype="bf16")
+    g = 8
+    print("few-token groups, backward %s" % backward, flush=True)
+    P = synth.make_params(w, _bias(w) + 0.1)
+    W_o, X = synth.make_out_proj(w).cuda(), synth.make_embeddings(w).cuda()
+    dims = _gdims(wm, w, groups=g, S_cap=w.T_new)
+    n = (wm.passes_backward_workspace(dims, 1) if backward
+         else wm.workspace_size(dims, wm.OP_PASSES))
+    ws = torch.full((n,), 255, dtype=torch.uint8, device="cuda")
+    Lp = (w.L + w.p - 1) // w.p
+    folds = 2 * (2 * w.k * w.L * Lp * w.D + 2 * w.k * w.Hkv * w.d * w.D)
+    if backward:
+        grads = {m: torch.zeros(t.shape, device="cuda") for m, t in P.items()}
+        dX, dW_o = torch.zeros(X.shape, device="cuda"), torch.zeros(W_o.shape, device="cuda")
+        dh = torch.ones(X.shape, device="cuda")
+        wm.prefill_passes_backward(dims, _dev(P), W_o, X, w.chan_map, 2, 1, dh, dX, dW_o, grads,
+                                   ws=ws)
+    else:
+        folds += 2 * w.L * w.Hq * w.d * w.D
+        shape = (w.k, w.B, w.Hkv, w.T_new, w.d)
+        Kc = torch.zeros(shape, dtype=torch.bfloat16, device="cuda")
+        H = torch.empty((w.B, w.T_new, w.L, w.D), dtype=torch.bfloat16, device="cuda")
+        wm.prefill_passes(dims, _dev(P), W_o, X, w.chan_map, 2, Kc, torch.zeros_like(Kc), H, ws=ws)
+    torch.cuda.synchronize()
+    fw = wm.workspace_size(dims, wm.OP_PASSES)  # the forward's share lies first
+    assert int((ws[:fw] == 255).sum()) >= folds
