@@ -26,7 +26,7 @@ struct TileArgs {
   bf16* O;
   int B, T, L, Hq, Hkv, S_cap, mask_paper;
   int gs, gq, ctx_hi;  // query i of sequence b sits at position ctx_len[b] + gq + gs i
-  int n_qtiles, units; // grid = n_qtiles x units; a unit is a head of a (layer, sequence)
+  int n_qtiles;        // grid: n_qtiles for each head of each (layer, sequence)
   float scale_log2;
   LayerTable chan, lord;  // lord: consumers sorted by channel
 };
@@ -217,8 +217,8 @@ void launch_attend_tiles(const Shape& sh, const LayerTable& chan, const LayerTab
                          const bf16* Vd, const int32_t* ctx_len, bf16* O, hipStream_t s) {
   const TileArgs a{Q, Kc, Vc, Kd, Vd, ctx_len, O, sh.B, sh.T_new, sh.L, sh.Hq, sh.Hkv, sh.S_cap,
                    sh.mask_paper, sh.gs, sh.gq, sh.ctx_hi, (sh.T_new + 31) / 32,
-                   sh.B * sh.L * sh.Hq, kLog2e / sqrtf((float)sh.d), chan, lord};
-  const dim3 grid((unsigned)(a.n_qtiles * a.units));
+                   kLog2e / sqrtf((float)sh.d), chan, lord};
+  const dim3 grid((unsigned)(a.n_qtiles * sh.B * sh.L * sh.Hq));
   if (sh.d == 64)
     hipLaunchKernelGGL(attend_tile_kernel<64>, grid, dim3(TileCfg<64>::NT), 0, s, a);
   else
