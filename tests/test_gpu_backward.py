@@ -16,11 +16,16 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T_new,ctx", [(40, 0), (300, 0), (70, 130)])
 @pytest.mark.parametrize("mask_mode", [0, 1])
 @pytest.mark.parametrize("d,Hq,Hkv,B", [(64, 4, 2, 2), (96, 6, 3, 2), (64, 2, 2, 2),
-                                        (64, 4, 2, 4), (96, 6, 3, 4)])
+                                        (64, 4, 2, 4), (96, 6, 3, 4), (64, 4, 2, 9),
+                                        (96, 6, 3, 9)])
 def test_channel_attend_backward(wm, T_new, ctx, mask_mode, d, Hq, Hkv, B):
     """B = 4 with Hkv = 2 gives 24 slices (channel, sequence, KV head): with their few slot
     tiles, the slot-major grid takes each XCD's heavy tiles first (slices a multiple of 8);
-    Hkv = 3 at B = 4 does not divide and keeps the slice-major order."""
+    Hkv = 3 at B = 4 does not divide and keeps the slice-major order. The query side: 32-row
+    tiles whose four waves cut the slots up to one of them per CU at head dim 96 (B = 2 at
+    T_new = 40 and 70: 120, 180) and two at 64, two waves up to three per CU at 96 (B = 4 at
+    T_new = 40 and 70: 240, 360; B = 9 at 40: 540), rows split among the waves past that (B = 9
+    at T_new = 70 and 300: 540 at head dim 64, 810 at 96, and more), with a cached context too."""
     w = synth.small("bwd_d%d" % d, B=B, T_new=T_new, L=5, k=3, D=64, Hq=Hq, Hkv=Hkv, d=d,
                     ctx=ctx + T_new, dtype="bf16", chan_map=[2, 0, 2, 2, 0])
     print("attention backward d%d %d/%d T%d ctx%d mask%d" % (d, Hq, Hkv, T_new, ctx, mask_mode),
@@ -28,7 +33,7 @@ def test_channel_attend_backward(wm, T_new, ctx, mask_mode, d, Hq, Hkv, B):
     P = synth.make_params(w, _bias(w))
     Q = synth.make_queries(w)
     Kc, Vc = synth.make_cache_cpu(w)
-    ctx_len = torch.tensor([ctx, ctx // 2, ctx // 3, ctx][:B], dtype=torch.int32)
+    ctx_len = torch.tensor([ctx // (1 + b % 3) for b in range(B)], dtype=torch.int32)
     od = _odims(w, mask_mode=mask_mode)
     O = oracle.channel_attend(od, P, Q, w.chan_map, ctx_len.numpy(), _f64(Kc), _f64(Vc))
     O_bf = torch.from_numpy(O).to(torch.bfloat16)
@@ -166,17 +171,20 @@ def test_channel_attend_backward_at_full_size(wm, name):
 
 @pytest.mark.parametrize("mask_mode", [0, 1])
 @pytest.mark.parametrize("d,Hq,Hkv", [(64, 4, 2), (96, 6, 3)])
-def test_channel_attend_backward_strided_group(wm, mask_mode, d, Hq, Hkv):
+@pytest.mark.parametrize("B", [2, 9])
+def test_channel_attend_backward_strided_group(wm, B, mask_mode, d, Hq, Hkv):
     """Queries of the strided token group q = 2 of g = 3 (positions ctx + 2 + 3 i, Section
-    3.3) over a cache whose every slot is given."""
+    3.3) over a cache whose every slot is given: 120 and 180 tiles of 32 rows, whose waves cut
+    the slots, and 540 (past two per CU at head dim 64) and 810 (past three at 96), which take
+    the kernel whose waves split the rows."""
     g, q, T_new, ctx = 3, 2, 90, 40
-    w = synth.small("bwd_grp_d%d" % d, B=2, T_new=T_new, L=5, k=3, D=64, Hq=Hq, Hkv=Hkv, d=d,
+    w = synth.small("bwd_grp_d%d" % d, B=B, T_new=T_new, L=5, k=3, D=64, Hq=Hq, Hkv=Hkv, d=d,
                     ctx=ctx + q + g * (T_new - 1) + 1, dtype="bf16", chan_map=[2, 0, 2, 1, 0])
-    print("attention backward strided group d%d mask%d" % (d, mask_mode), flush=True)
+    print("attention backward strided group d%d mask%d B%d" % (d, mask_mode, B), flush=True)
     P = synth.make_params(w, _bias(w))
     Q = synth.make_queries(w)
     Kc, Vc = synth.make_cache_cpu(w)  # every slot below the span holds values
-    ctx_len = torch.tensor([ctx, ctx // 2], dtype=torch.int32)
+    ctx_len = torch.tensor([ctx // (1 + b % 3) for b in range(B)], dtype=torch.int32)
     od = _odims(w, mask_mode=mask_mode)
     O = ob.attend(od, ob._t(P["Kd"]), ob._t(P["Vd"]), ob._t(Q), w.chan_map,
                   torch.as_tensor(ctx_len.numpy(), dtype=torch.long), ob._t(Kc), ob._t(Vc),

@@ -72,6 +72,45 @@ def test_few_token_step(wm, d, mode, B, T_new, D, p, ctx):
     check_close(O, Oo, "bf16", "few-token step %s" % mode)
 
 
+# (d, k, Hq, Hkv, B, T_new, ctx, waves a workgroup)
+STREAM_CASES = [(96, 8, 6, 3, 8, 4, 4000, 2), (64, 6, 8, 8, 16, 1, 2000, 2),
+                (64, 12, 16, 16, 28, 1, 100, 1), (96, 12, 16, 16, 20, 2, 98, 1)]
+
+
+@pytest.mark.parametrize("docs", [False, True])
+@pytest.mark.parametrize("d,k,Hq,Hkv,B,T_new,ctx,waves", STREAM_CASES)
+def test_streamed_cache(wm, d, k, Hq, Hkv, B, T_new, ctx, waves, docs):
+    """Caches just past 128 MB, whose slots are copied without keeping them in the caches
+    (non-temporal), with and without documents, by workgroups of two waves and (walks of at
+    most 128 slots) one: the first and the last sequence against the oracle."""
+    w = synth.small("stream_d%d" % d, B=B, T_new=T_new, L=k, k=k, D=64, Hq=Hq, Hkv=Hkv, d=d,
+                    ctx=ctx + T_new, dtype="bf16")
+    print("streamed cache d%d k%d B%d T%d ctx%d docs %s" % (d, k, B, T_new, ctx, docs), flush=True)
+    kend = ctx + T_new
+    assert 4 * k * B * Hkv * kend * d >= 128 << 20
+    length, slices = 4096, k * B * Hkv
+    while length > 256 and slices * -(-kend // length) < 512:
+        length //= 2
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    wgs = slices * -(-kend // length)
+    four = wgs <= cus if d == 96 else wgs > 5 * cus and min(kend, length) >= 1024
+    assert waves == (1 if min(kend, length) <= 128 else 4 if four else 2)
+    P = synth.make_params(w, _bias(w))
+    Q = synth.make_queries(w)
+    Kc, Vc = synth.make_cache_device(w, fill=0.0)
+    ctx_len = torch.tensor([ctx - 7 * (b % 5) for b in range(B)], dtype=torch.int32)
+    doc = synth.make_doc_start(w, ctx_len, mean_len=61.0) if docs else None
+    O = torch.full((k, B, T_new, Hq * d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wm.channel_attend(_gdims(wm, w, ctx_max=ctx), _dev(P), Q.cuda(), w.chan_map, ctx_len.cuda(),
+                      Kc, Vc, O, doc_start=doc.cuda() if docs else None)
+    torch.cuda.synchronize()
+    at = [0, B - 1]
+    ref = oracle.channel_attend(_odims(w, B=2), P, Q[:, at], w.chan_map, ctx_len[at].numpy(),
+                                _f64(Kc[:, at]), _f64(Vc[:, at]),
+                                doc_start=doc[at].numpy() if docs else None)
+    check_close(O[:, at], ref, "bf16", "streamed d%d B%d docs %s" % (d, B, docs))
+
+
 @pytest.mark.parametrize("k", [1, 12])
 @pytest.mark.parametrize("B,ctx", [(1, 8191), (2, 4000)])
 def test_one_layer_splits_its_own_channel(wm, k, B, ctx):

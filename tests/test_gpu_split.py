@@ -4,7 +4,8 @@ their partial softmax states (Section 3.1 Step 3: one softmax over the visible s
 Section 3.2: the dummy slot starts the row, so it belongs to the first range only).
 
 Each case first checks on the host that the kernel's planner splits it (query tiles at
-most a quarter of the workgroups the CUs hold, walks of at least 32 64-slot blocks), then compares
+most a quarter of the workgroups the CUs hold, walks of at least 32 64-slot blocks, and past the
+3072 slots up to which 32-row tiles whose waves cut the slots take so few rows), then compares
 every output element with the oracle: contiguous tokens and one strided token group, both
 masks, head dims 64 and 96 with grouped heads, a sequence whose shorter context leaves
 some of its tiles' ranges empty, and peaked scores (the sawtooth keys of the rescale
@@ -26,7 +27,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("mask_mode", [0, 1])
 @pytest.mark.parametrize("g,q,peak", [(1, 0, False), (3, 2, False), (1, 0, True)])
 def test_channel_attend_split_ranges(wm, d, Hq, Hkv, mask_mode, g, q, peak):
-    T_new, ctx = 96, 2200
+    T_new, ctx = 96, 3200
     span = q + g * (T_new - 1) + 1
     w = synth.small("split_d%d" % d, B=2, T_new=T_new, L=2, k=1, D=64, Hq=Hq, Hkv=Hkv, d=d,
                     ctx=ctx + span, dtype="bf16", chan_map=[0, 0])
@@ -34,6 +35,7 @@ def test_channel_attend_split_ranges(wm, d, Hq, Hkv, mask_mode, g, q, peak):
     resident = torch.cuda.get_device_properties(0).multi_processor_count * (3 if d == 64 else 2)
     blocks = (ctx + span + 63) // 64
     assert 4 * tiles <= resident and blocks >= 32, (tiles, resident, blocks)
+    assert ctx + span > 3072
     print("split ranges d%d mask%d g%d q%d peaked %s: %d tiles, %d blocks"
           % (d, mask_mode, g, q, peak, tiles, blocks), flush=True)
     P = synth.make_params(w, _bias(w))

@@ -63,9 +63,23 @@ def test_split_ranges_past_the_tiles_walk(wm, d, Hq, Hkv):
     assert slots > 3072 and slots // 64 >= 32
 
 
-@pytest.mark.parametrize("d,Hq,Hkv,L", [(96, 6, 3, 3), (96, 6, 3, 5), (64, 4, 2, 3), (96, 6, 3, 11),
-                                        (64, 4, 2, 25)])
-def test_strided_groups_of_two_heads(wm, d, Hq, Hkv, L):
-    """Heads that divide among the XCDs (L = 3) and not (5), and more tiles than the CUs hold
-    at once (11, 25: the work queue); the last tile of 100 queries is partial."""
-    _case(wm, d, Hq, Hkv, 100, 40, [40, 0, 7, 33, 1, 2, 39, 20], 4, 3, 0, False, L=L)
+@pytest.mark.parametrize("d,Hq,Hkv,L,B,order", [(96, 6, 3, 3, 8, "bands"), (96, 6, 3, 5, 8, "bands"),
+                                                (64, 4, 2, 3, 8, "bands"),
+                                                (96, 6, 3, 5, 7, "tiles"),
+                                                (64, 4, 2, 5, 7, "tiles"),
+                                                (96, 6, 3, 11, 8, "queue"),
+                                                (64, 4, 2, 25, 8, "queue")])
+def test_strided_groups_of_two_heads(wm, d, Hq, Hkv, L, B, order):
+    """Pairs of heads that divide among the 8 XCDs (a band of them each, longest tiles first) and
+    that do not (tile order), and more tiles than the CUs hold at once (the work queue); the
+    last tile of 100 queries is partial."""
+    T_new = 100
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rows, slots = _case(wm, d, Hq, Hkv, T_new, 40, [40, 0, 7, 33, 1, 2, 39, 20][:B], 4, 3, 0,
+                        False, L=L)
+    tiles = (T_new + 127) // 128 * Hq * B * L
+    resident = cus * (3 if d == 64 else 2)
+    # neither the few-row tiles (one per CU at most) nor split ranges (from 32 blocks of 64)
+    assert rows > cus and slots < 2048
+    units = Hq // 2 * B * L
+    assert order == ("queue" if tiles > resident else "tiles" if units % 8 else "bands")

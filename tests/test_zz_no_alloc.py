@@ -41,9 +41,12 @@ def test_static_scratch_matches_workspace_entry_point(wm, dtype, d):
                      dtype=dtype), 3000),
         (synth.small("static_prefill", B=2, T_new=40, L=3, k=2, D=64, Hq=2, Hkv=1, d=d, ctx=140,
                      dtype=dtype), 100),
-        # few query tiles over a 2000-slot context: the bf16 kernel splits the slot ranges
-        (synth.small("static_split", B=2, T_new=40, L=3, k=2, D=64, Hq=2, Hkv=1, d=d, ctx=2240,
+        # few query tiles over a 2200-slot context: 32-row tiles whose waves cut the slots (bf16)
+        (synth.small("static_tiles", B=2, T_new=40, L=3, k=2, D=64, Hq=2, Hkv=1, d=d, ctx=2240,
                      dtype=dtype), 2200),
+        # past 3072 slots: split slot ranges, whose partial states use the scratch
+        (synth.small("static_split", B=2, T_new=40, L=3, k=2, D=64, Hq=2, Hkv=1, d=d, ctx=3340,
+                     dtype=dtype), 3300),
     ]
     for w, ctx in cases:
         print("static scratch", w.name, dtype, d, flush=True)
