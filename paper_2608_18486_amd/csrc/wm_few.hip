@@ -44,7 +44,7 @@ __device__ __forceinline__ float few_product(__amdgpu_buffer_rsrc_t wv, uint32_t
                                              f32x16 (&acc)[NDT], char* area, int lane) {
   using F = FewTile<NDT>;
   const int h = lane >> 5, r = lane & 31;
-  float ss = 0.f, sg = 0.f;
+  LongSum ss;
   const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)area);
   for (int kb = k0; kb < k1; kb += 16 * kFewBatch) {
 #pragma unroll
@@ -66,7 +66,7 @@ __device__ __forceinline__ float few_product(__amdgpu_buffer_rsrc_t wv, uint32_t
         v[i] = *(const f32x2*)(sq + min(kb + 16 * (kFewBatch / 2 * h + i), k1 - 16) / 8);
 #pragma unroll
       for (int i = 0; i < kFewBatch / 2; ++i)
-        sg += kb + 16 * (kFewBatch / 2 * h + i) < k1 ? v[i][0] + v[i][1] : 0.f;
+        ss.add(kb + 16 * (kFewBatch / 2 * h + i) < k1 ? v[i][0] + v[i][1] : 0.f);
     }
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
 #pragma unroll
@@ -75,18 +75,16 @@ __device__ __forceinline__ float few_product(__amdgpu_buffer_rsrc_t wv, uint32_t
       const bf16x8 xf = *(const bf16x8*)(area + (32 * NDT + r) * 256 + c);
       bf16x8 xg;
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const float v = (float)xf[t];
-        ss += v * v;
-        xg[t] = (bf16)(v * (float)gf[i][t]);
-      }
+      for (int t = 0; t < 8; ++t)
+        xg[t] = (bf16)((float)xf[t] * (float)gf[i][t]);
+      if (!sq) ss.add(squares8(xf));
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt)
         acc[dt] = mma32(acc[dt], *(const bf16x8*)(area + (32 * dt + r) * 256 + c), xg);
     }
     asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the area takes the next batch
   }
-  return halves_sum(sq ? sg : ss);
+  return halves_sum(ss.total());
 }
 
 struct FewProj {

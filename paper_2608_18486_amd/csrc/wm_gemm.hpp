@@ -302,9 +302,7 @@ __global__ __launch_bounds__(C::NT) void proj_gemm_dma_kernel(int M, int Nout, i
 #pragma unroll
     for (int j = 0; j < C::WN; ++j) acc[i][j] = zero16();
 
-  float ss[C::WN];  // kOwnRms: this lane's share of its tokens' sums of squares
-#pragma unroll
-  for (int j = 0; j < C::WN; ++j) ss[j] = 0.f;
+  LongSum ss[C::WN];  // kOwnRms: this lane's share of its tokens' sums of squares
   auto compute = [&](int stage) {
     const T* Ws = smem + stage * D::ROWS_PAD * 32;
     const T* Xs = Ws + C::OT * 32;
@@ -323,9 +321,7 @@ __global__ __launch_bounds__(C::NT) void proj_gemm_dma_kernel(int M, int Nout, i
         for (int j = 0; j < C::WN; ++j) acc[i][j] = mma32(acc[i][j], a[i], b[j]);
       if constexpr (OwnRms<Epi>::value) {
 #pragma unroll
-        for (int j = 0; j < C::WN; ++j)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) ss[j] = fmaf((float)b[j][e], (float)b[j][e], ss[j]);
+        for (int j = 0; j < C::WN; ++j) ss[j].add(squares8(b[j]));
       }
     }
   };

@@ -450,12 +450,12 @@ template <typename T, int DH, bool RMS = false> struct QEpi {
     float rinv[4];  // RMS: of this lane's tokens
   };
   template <class C>
-  __device__ void row_squares(int l, int ow0, int nw0, float (&ss)[C::WN], int K, int lane,
+  __device__ void row_squares(int l, int ow0, int nw0, LongSum (&ss)[C::WN], int K, int lane,
                               State& st) const {
     static_assert(C::WN <= 4, "the state holds every token of a lane");
 #pragma unroll
     for (int j = 0; j < C::WN; ++j) {
-      st.rinv[j] = 1.0f / sqrtf(halves_sum(ss[j]) / (float)K + eps);
+      st.rinv[j] = 1.0f / sqrtf(halves_sum(ss[j].total()) / (float)K + eps);
       const int n = nw0 + 32 * j + (lane & 31);
       if (ow0 == 0 && lane < 32 && n < M) rs[(long)n * L + l0 + l] = st.rinv[j];
     }
@@ -1366,7 +1366,8 @@ void launch_q_layers(const Shape& sh, const T* H, const float* rinv, const T* g_
 // One layer, its input norm included. On small tiles (bf16) the product sums the squares of
 // the rows it reads anyway (a launch of its own for the norm: 3.8 us of a 52 us layer at 1024
 // tokens, 5.3 of 95 at 8192); large ones, whose blocks would each repeat the sums for their
-// channel tile, take the norms from row_rms.
+// channel tile, take the norms from row_rms. The sums carry their rounding (LongSum), about 1% of
+// a pass of the 16-layer model at 1024 tokens a group.
 template <typename T>
 void launch_layer_queries(const Shape& sh, const T* H, float* rinv, const T* g_qnorm,
                           const float* rope_tab, T* Q, const T* wfold, int l, hipStream_t s) {

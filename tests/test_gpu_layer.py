@@ -99,3 +99,38 @@ def test_one_layer_pass(wm, B, T, D, Hq, Hkv, d):
     # what is left: the fp32 sum of Hq d terms, 2^-24 of the terms for each step at most
     terms = X.double().abs() + O[0].double().abs() @ W_o[0].double().abs().t()
     assert bool((off <= 2.0 ** -24 * Hq * d * terms).all()), float((off / terms).max())
+
+
+@pytest.mark.parametrize("D", [512, 2048, 4608])
+@pytest.mark.parametrize("d,Hq", [(64, 4), (96, 3)])
+def test_own_norm_keeps_fp32(wm, d, Hq, D):
+    """The norm that a product makes of the rows it reads (1 / RMS, left at the head of the
+    workspace) against float64. Roundings of 2^-24 in the sum: four for 8 squares added in
+    pairs, three for the sums' own with the rounding of each carried along, one where the halves
+    of a row join, two for the mean and eps; half of these ten pass the root, which adds its own
+    and the division's. Squares added one after the other are off by 20 such roundings at
+    D = 2048 and 50 at 4608."""
+    B, L = 80, 2
+    gen = torch.Generator().manual_seed(9)
+
+    def normal(*shape):
+        return torch.empty(shape).normal_(generator=gen).bfloat16().cuda()
+
+    print("own norm D%d d%d" % (D, d), flush=True)
+    P = {n: torch.zeros(8, dtype=torch.bfloat16, device="cuda") for n in wm.PARAM_NAMES}
+    P.update(Kd=normal(1, Hq, d), Vd=normal(1, Hq, d), g_in=normal(L, D), Wq=normal(L, Hq * d, D),
+             g_qnorm=normal(L, d))
+    H = normal(B, 5, L, D)
+    dims = wm.make_dims(B, 5, L, 1, D, Hq, Hq, d, S_cap=64, dtype=wm.BF16, eps=EPS)
+    Kc = torch.zeros((1, B, Hq, 64, d), dtype=torch.bfloat16, device="cuda")
+    O = torch.empty((B, 5, Hq * d), dtype=torch.bfloat16, device="cuda")
+    ws = wm.workspace(dims, wm.OP_LAYER_ATTEND)
+    ctx = torch.zeros(B, dtype=torch.int32, device="cuda")
+    wm.layer_attend(dims, P, 1, H, [0, 0], ctx, Kc, torch.zeros_like(Kc), O, ws=ws)
+    torch.cuda.synchronize()
+    got = ws[:4 * B * 5 * L].view(torch.float32).reshape(B, 5, L)[:, :, 1].double()
+    x = H[:, :, 1].double()
+    ref = torch.rsqrt((x * x).mean(-1) + EPS)
+    worst = float((got / ref - 1).abs().max())
+    print("worst %.2g" % worst)
+    assert worst <= 7 * 2.0 ** -24, worst
