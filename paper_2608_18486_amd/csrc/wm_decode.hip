@@ -1,10 +1,9 @@
 // Decode form of the channel attention (paper Section 3.1 Step 3, Section 3.2): few new
 // tokens per sequence (T_new <= 4) against a long cache.
 //
-// Split-S over the cache, one
-// workgroup per (split, channel, sequence, KV head) serving every query row
-// that reads that channel and head (all its consumer layers, grouped query
-// heads and new tokens), so each channel slice is streamed from HBM once.
+// Split-S over the cache, one workgroup per (split, channel with a reader, sequence, KV head)
+// serving every query row that reads that channel and head (all its consumer layers, grouped
+// query heads and new tokens), so each channel slice is streamed from HBM once.
 #include <algorithm>
 
 #include "wm_device.hpp"
@@ -50,8 +49,9 @@ template <typename T> struct DecodeArgs {
   int gs, gq, ctx_hi;  // query i of sequence b sits at position ctx_len[b] + gq + gs i
   float scale_log2;
   LayerTable chan;
+  // the grid's channels, those with a reader: live[i], its consumers offsets[i] .. offsets[i + 1]
+  LayerTable live;
   ChannelGroups cg;
-  LayerTable live;  // the channels with a reader: the grid's channels
 };
 
 // Merge online-softmax state (m2, l2, o2) into (m, l, o).
@@ -124,8 +124,8 @@ void attend_decode_mfma_kernel(DecodeArgs<bf16> a) {
   int y = blockIdx.y;
   const int kvh = y % a.Hkv;
   y /= a.Hkv;
-  const int b = y % a.B, c = a.live.v[y / a.B];
-  const int off = a.cg.offsets[c], nmem = a.cg.offsets[c + 1] - off;
+  const int b = y % a.B, ci = y / a.B, c = a.live.v[ci];
+  const int off = a.cg.offsets[ci], nmem = a.cg.offsets[ci + 1] - off;
   const int grp = a.Hq / a.Hkv;
   const int G = nmem * grp * a.T_new, g0 = 32 * blockIdx.z;
   if (g0 >= G) return;
@@ -328,8 +328,8 @@ __global__ __launch_bounds__(256) void attend_decode_kernel(DecodeArgs<T> a) {
   int y = blockIdx.y;
   const int kvh = y % a.Hkv;
   y /= a.Hkv;
-  const int b = y % a.B, c = a.live.v[y / a.B];
-  const int off = a.cg.offsets[c], nmem = a.cg.offsets[c + 1] - off;
+  const int b = y % a.B, ci = y / a.B, c = a.live.v[ci];
+  const int off = a.cg.offsets[ci], nmem = a.cg.offsets[ci + 1] - off;
   const int grp = a.Hq / a.Hkv;
   const int G = nmem * grp * a.T_new;
   // position of query i: pos0 + gs i (wave-uniform)
@@ -570,16 +570,17 @@ static void decode_mfma(DecodeArgs<bf16> a, int G, int nlive, const Shape& sh, h
   // layers' calls read theirs in between) than the caches keep from call to call
   const bool once = z == 1 && 4L * sh.k * sh.B * sh.Hkv * kend * DH >= kDecodeStreamBytes;
   // Waves per workgroup: 2, which leaves a CU's LDS to five workgroups (three at head dim
-  // 96); 1 where a workgroup's walk is at most 128 slots (four blocks); 4 at head dim 96
-  // where the workgroups do not outnumber the CUs, and at head dim 64 for long walks in
-  // several rounds of workgroups. Attention alone with 1 / 2 / 4 waves, us: ctx 100, B 64, L 24, k 12,
-  // heads of 64: 77 / 87 / 111; ctx 4000, B 4: 172 / 126 / 133; ctx 1500, B 16, L 12: 144 /
-  // 156 / 144; ctx 3000, B 24: 426 / 424 / 400; heads of 96, k = 8: ctx 1000, B 4: 19 / 16.7 /
-  // 18.7; ctx 8000, B 1, k = 2: 31 / 26 / 23.6.
-  const long wgs = a.nsplit * slices, per = std::min<long>(kend, len);
-  const int waves = per <= 128 ? 1
-                    : (DH == 96 ? wgs <= device_cus() : wgs > 5L * device_cus() && per >= 1024)
-                        ? 4 : 2;
+  // 96); 1 where a workgroup's walk is at most 128 slots (four blocks); 4 where the workgroups
+  // fit the CUs all at once with four (one per CU at head dim 96, two at 64), and at head dim
+  // 64 for long walks in several rounds of workgroups. Attention alone with 1 / 2 / 4 waves, us:
+  // ctx 100, B 64, L 24, k 12, heads of 64: 77 / 87 / 111; ctx 4000, B 4: 172 / 126 / 133; ctx
+  // 1500, B 16, L 12: 144 / 156 / 144; ctx 3000, B 24: 426 / 424 / 400; heads of 96, k = 8: ctx
+  // 1000, B 4: 19 / 16.7 / 18.7; ctx 8000, B 1, k = 2: 31 / 26 / 23.6. One layer of 16 heads of
+  // 64 with its query, 2 / 4 waves: ctx 700, B 1 19.6 / 19.1; ctx 3000, B 8 38.9 / 33.5; ctx 7948,
+  // B 8 62.5 / 57.7; of 12 heads 60.1 / 48.2.
+  const long wgs = a.nsplit * slices, per = std::min<long>(kend, len), cus = device_cus();
+  const bool four = DH == 96 ? wgs <= cus : wgs <= 2 * cus || (wgs > 5 * cus && per >= 1024);
+  const int waves = per <= 128 ? 1 : four ? 4 : 2;
 #define WM_DEC_GO(NW, DOC, ONCE)                                                              \
   hipLaunchKernelGGL((attend_decode_mfma_kernel<DH, NW, DOC, ONCE>), grid, dim3(64 * (NW)), 0, \
                      s, a)
@@ -611,13 +612,16 @@ void launch_attend_decode(const Shape& sh, const LayerTable& chan_map, const Cha
   if (sh.N() <= 0) return;
   DecodeArgs<T> a{Q, Kc, Vc, Kd, Vd, ctx_len, doc, partials, O, sh.B, sh.T_new, sh.L, sh.Hq, sh.Hkv,
                   sh.S_cap, sh.mask_paper, decode_splits(sh), decode_split_len(sh), sh.gs, sh.gq,
-                  sh.ctx_hi, kLog2e / sqrtf((float)sh.d), chan_map, cg, {}};
+                  sh.ctx_hi, kLog2e / sqrtf((float)sh.d), chan_map, {}, cg};
   int maxmem = 0, nlive = 0;
   for (int c = 0; c < sh.k; ++c) {
     int n = cg.offsets[c + 1] - cg.offsets[c];
-    if (n > 0) a.live.v[nlive++] = c;
+    if (n == 0) continue;
+    a.cg.offsets[nlive] = cg.offsets[c];
+    a.live.v[nlive++] = c;
     if (n > maxmem) maxmem = n;
   }
+  a.cg.offsets[nlive] = cg.offsets[sh.k];
   int G = maxmem * (sh.Hq / sh.Hkv) * sh.T_new;
   dim3 grid(a.nsplit, sh.Hkv * sh.B * nlive);
   if constexpr (sizeof(T) == 2) {  // fp32 at d = 96 is rejected by validation

@@ -44,7 +44,9 @@ __device__ __forceinline__ float few_product(__amdgpu_buffer_rsrc_t wv, uint32_t
                                              f32x16 (&acc)[NDT], char* area, int lane) {
   using F = FewTile<NDT>;
   const int h = lane >> 5, r = lane & 31;
-  LongSum ss;
+  // eight sums of D / 64 terms at most: one of all of them is off by 4e-7 at D = 512 and more
+  // past it, these by 1e-7, as a row's norm in a kernel of its own
+  float ss[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, sg = 0.f;
   const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)area);
   for (int kb = k0; kb < k1; kb += 16 * kFewBatch) {
 #pragma unroll
@@ -66,7 +68,7 @@ __device__ __forceinline__ float few_product(__amdgpu_buffer_rsrc_t wv, uint32_t
         v[i] = *(const f32x2*)(sq + min(kb + 16 * (kFewBatch / 2 * h + i), k1 - 16) / 8);
 #pragma unroll
       for (int i = 0; i < kFewBatch / 2; ++i)
-        ss.add(kb + 16 * (kFewBatch / 2 * h + i) < k1 ? v[i][0] + v[i][1] : 0.f);
+        sg += kb + 16 * (kFewBatch / 2 * h + i) < k1 ? v[i][0] + v[i][1] : 0.f;
     }
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
 #pragma unroll
@@ -75,16 +77,19 @@ __device__ __forceinline__ float few_product(__amdgpu_buffer_rsrc_t wv, uint32_t
       const bf16x8 xf = *(const bf16x8*)(area + (32 * NDT + r) * 256 + c);
       bf16x8 xg;
 #pragma unroll
-      for (int t = 0; t < 8; ++t)
-        xg[t] = (bf16)((float)xf[t] * (float)gf[i][t]);
-      if (!sq) ss.add(squares8(xf));
+      for (int t = 0; t < 8; ++t) {
+        const float v = (float)xf[t];
+        ss[t] = fmaf(v, v, ss[t]);
+        xg[t] = (bf16)(v * (float)gf[i][t]);
+      }
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt)
         acc[dt] = mma32(acc[dt], *(const bf16x8*)(area + (32 * dt + r) * 256 + c), xg);
     }
     asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the area takes the next batch
   }
-  return halves_sum(ss.total());
+  const float sx = ((ss[0] + ss[1]) + (ss[2] + ss[3])) + ((ss[4] + ss[5]) + (ss[6] + ss[7]));
+  return halves_sum(sq ? sg : sx);
 }
 
 struct FewProj {

@@ -93,7 +93,7 @@ def test_streamed_cache(wm, d, k, Hq, Hkv, B, T_new, ctx, waves, docs):
         length //= 2
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     wgs = slices * -(-kend // length)
-    four = wgs <= cus if d == 96 else wgs > 5 * cus and min(kend, length) >= 1024
+    four = wgs <= cus if d == 96 else wgs <= 2 * cus or (wgs > 5 * cus and min(kend, length) >= 1024)
     assert waves == (1 if min(kend, length) <= 128 else 4 if four else 2)
     P = synth.make_params(w, _bias(w))
     Q = synth.make_queries(w)
