@@ -228,9 +228,9 @@ def _strip_comments(src: str) -> str:
 
 
 KERNEL_SOURCES = {
-    "attend": ("wm_attend.hip", "wm_device.hpp", "wm_frag.hpp"),
+    "attend": ("wm_attend.hip", "wm_decode.hip", "wm_tile.hip", "wm_device.hpp", "wm_frag.hpp"),
 }
-POOL_SOURCES = ("wm_pool.hip", "wm_gemm.hpp", "wm_device.hpp")
+POOL_SOURCES = ("wm_pool.hip", "wm_few.hip", "wm_gemm.hpp", "wm_device.hpp")
 
 
 def _kernel_source_hash(phase=None):
@@ -826,8 +826,9 @@ def main():
     mix = "mix_mfma_kernel" if (w.dtype == "bf16" and w.L <= 32 and w.k <= 32) else "mix_kernel"
     prefill = "attend_prefill_dma_kernel" if (w.dtype == "bf16" and w.d in (64, 96)) else \
         "attend_prefill_kernel"
-    roof["kernel"] = {"attend": prefill if w.T_new > 4 else
-                      "attend_decode_kernel + attend_combine_kernel",
+    decode = "attend_decode_mfma_kernel" if (w.dtype == "bf16" and w.d in (64, 96)) else \
+        "attend_decode_kernel"
+    roof["kernel"] = {"attend": prefill if w.T_new > 4 else decode + " + attend_combine_kernel",
                       "kv_project": gemm + " (K/V projection, after fold_gain_kernel)",
                       "q_project": gemm + " (Q projection, after fold_gain_kernel)",
                       "router": gemm + " (router, with router_fold/reduce kernels)",

@@ -135,8 +135,7 @@ def test_layer_step_with_context(wm, T_new, mask_mode):
 @pytest.mark.parametrize("T_new", [1, 3, 33])
 @pytest.mark.parametrize("mask_mode", [0, 1])
 def test_layer_step_with_context_d96(wm, T_new, mask_mode):
-    """Head dim 96: decode (12 of 16 lanes per slot group) and chunked prefill over a
-    ragged cached context."""
+    """Head dim 96: decode and chunked prefill over a ragged cached context."""
     w = synth.small("ctx_d96_T%d" % T_new, B=3, T_new=T_new, L=6, k=3, D=192, Hq=6, Hkv=3,
                     d=96, ctx=700, p=2)
     _layer_step_case(wm, w, mask_mode=mask_mode, ragged=True)
