@@ -306,6 +306,9 @@ __global__ __launch_bounds__(C::NT) void proj_gemm_dma_kernel(int M, int Nout, i
   auto compute = [&](int stage) {
     const T* Ws = smem + stage * D::ROWS_PAD * 32;
     const T* Xs = Ws + C::OT * 32;
+    float sq[C::WN];
+#pragma unroll
+    for (int j = 0; j < C::WN; ++j) sq[j] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < C::BK / 16; ++ks) {
       frag_t<T> a[C::WO], b[C::WN];
@@ -321,8 +324,12 @@ __global__ __launch_bounds__(C::NT) void proj_gemm_dma_kernel(int M, int Nout, i
         for (int j = 0; j < C::WN; ++j) acc[i][j] = mma32(acc[i][j], a[i], b[j]);
       if constexpr (OwnRms<Epi>::value) {
 #pragma unroll
-        for (int j = 0; j < C::WN; ++j) ss[j].add(squares8(b[j]));
+        for (int j = 0; j < C::WN; ++j) sq[j] += squares8(b[j]);
       }
+    }
+    if constexpr (OwnRms<Epi>::value) {
+#pragma unroll
+      for (int j = 0; j < C::WN; ++j) ss[j].add(sq[j]);
     }
   };
 

@@ -105,9 +105,9 @@ def test_one_layer_pass(wm, B, T, D, Hq, Hkv, d):
 @pytest.mark.parametrize("d,Hq", [(64, 4), (96, 3)])
 def test_own_norm_keeps_fp32(wm, d, Hq, D):
     """The norm that a product makes of the rows it reads (1 / RMS, left at the head of the
-    workspace) against float64. Roundings of 2^-24 in the sum: four for 8 squares added in
-    pairs, three for the sums' own with the rounding of each carried along, one where the halves
-    of a row join, two for the mean and eps; half of these ten pass the root, which adds its own
+    workspace) against float64. Roundings of 2^-24 in the sum: five for 16 squares (four and one
+    where two eights join), three for the sums' own with the rounding of each carried along, one where the halves
+    of a row join, two for the mean and eps; half of these eleven pass the root, which adds its own
     and the division's. Squares added one after the other are off by 20 such roundings at
     D = 2048 and 50 at 4608."""
     B, L = 80, 2
@@ -133,4 +133,4 @@ def test_own_norm_keeps_fp32(wm, d, Hq, D):
     ref = torch.rsqrt((x * x).mean(-1) + EPS)
     worst = float((got / ref - 1).abs().max())
     print("worst %.2g" % worst)
-    assert worst <= 7 * 2.0 ** -24, worst
+    assert worst <= 8 * 2.0 ** -24, worst
