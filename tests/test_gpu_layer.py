@@ -105,11 +105,11 @@ def test_one_layer_pass(wm, B, T, D, Hq, Hkv, d):
 @pytest.mark.parametrize("d,Hq", [(64, 4), (96, 3)])
 def test_own_norm_keeps_fp32(wm, d, Hq, D):
     """The norm that a product makes of the rows it reads (1 / RMS, left at the head of the
-    workspace) against float64. Roundings of 2^-24 in the sum: five for 16 squares (four and one
-    where two eights join), three for the sums' own with the rounding of each carried along, one where the halves
-    of a row join, two for the mean and eps; half of these eleven pass the root, which adds its own
-    and the division's. Squares added one after the other are off by 20 such roundings at
-    D = 2048 and 50 at 4608."""
+    workspace) against float64. Roundings of 2^-24 in the sum: five for 16 squares (four for
+    eight, one where two eights join), three for the sums' own with the rounding of each carried
+    along, one where the halves of a row join, two for the mean and eps; half of these eleven
+    pass the root, which adds its own and the division's. Squares added one after the other are
+    off by 20 such roundings at D = 2048 and 50 at 4608."""
     B, L = 80, 2
     gen = torch.Generator().manual_seed(9)
 
