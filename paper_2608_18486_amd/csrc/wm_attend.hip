@@ -1169,7 +1169,9 @@ void launch_attend_prefill(const Shape& sh, const LayerTable& chan_map, const T*
       // now: 32 tokens of 8 sequences 17.8 / 21.9 / 26.4 / 30.4 (split) -> 11.6 / 16.6 / 27.0 /
       // 46.4; of 32 sequences (192 tiles, not split) 18.0 / 29.0 / 50.8 / 96.3 -> 12.7 / 17.9 /
       // 28.7 / 62.7. With more workgroups than CUs it is slower than the tiles (128 tokens of
-      // 32 sequences: 35 -> 51 us at ctx 2000).
+      // 32 sequences: 35 -> 51 us at ctx 2000). Heads of 64 (12/12), ctx 1000 / 2000: 32
+      // tokens of 4 sequences 14.2 / 17.6 -> 10.3 / 12.8, 256 of 2 17.8 / 21.7 -> 10.1 / 14.3; at
+      // 4000 the split ranges keep them (21.5, 24.3).
       const long kmax = (long)sh.ctx_max + sh.span();
       const long rows32 = (long)((sh.T_new + 31) / 32) * sh.Hq * sh.B * sh.L;
       if (rows32 <= device_cus() && kmax >= 512 && (ad.nsplit == 1 || kmax <= 3072)) {
@@ -1183,7 +1185,9 @@ void launch_attend_prefill(const Shape& sh, const LayerTable& chan_map, const T*
     // tile walks the last one's range, so tiles of half the queries of two heads idle less,
     // and with the long ones first a CU pairs a long and a short one (64 sequences x 128
     // queries of a group of 16 over 2048 slots, 6/3 heads of 96: the 256 calls of four passes
-    // over four layers 13.8 -> 11.6 ms; in tile order 13.7).
+    // over four layers 13.8 -> 11.6 ms; in tile order 13.7). Heads of 64, one call, us: 8/4, 64 x 128
+    // queries of 16 groups 43.6 -> 36.1, 16 x 512 of 4 36.6 -> 30.9; 16/4, 64 x 64 of 16 37.7 ->
+    // 30.4, 32 x 256 of 8 68.3 -> 69.0; 32/8, 64 x 40 of 4 25.5 -> 18.4, 40 x 65 of 8 32.6 -> 33.1.
     long wgs = tiles;
     const bool pair = !doc && ad.nsplit == 1 && sh.gs >= 4 && sh.Hq / sh.Hkv % 2 == 0;
     if (pair) {

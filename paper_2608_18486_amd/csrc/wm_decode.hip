@@ -70,7 +70,7 @@ __device__ __forceinline__ void merge_state(float& m, float& l, float* o, float 
 // MFMAs, as in the full-sequence kernel, so a slot costs the same for 1 row and for 32.
 // (The VALU kernel below spends 16 fused multiply-adds and a butterfly per slot, lane and
 // row: at 16 rows, B = 8, ctx 4001, k = 8, 6/3 heads of 96 it ran 383 us on 221 MB of
-// cache; this one 65 us. At 2 rows and head dim 64 both run at the rate of the cache
+// cache; this one 47 us. At 2 rows and head dim 64 both run at the rate of the cache
 // stream at B = 16, ctx 8191, k = 12; at one consumer over 709 slots this one
 // takes 7 us and the VALU kernel 10.6.) What is left is the stream: each of NW waves walks
 // every NW-th 32-slot block through a ring of two blocks of its own in LDS (LDS-DMA, no
