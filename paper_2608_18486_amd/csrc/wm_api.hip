@@ -222,10 +222,8 @@ Layout layout(const wm_dims& dd, int op) {
     Ly.rinv = take(N * d.L * 4);
   if (op == WM_OP_ROUTER_MIX || all || pool) Ly.alpha = take(2 * N * d.k * d.L * 4);
   if (all || pool) Ly.mixed = take(2 * (size_t)d.k * N * d.D * es);
-  // the mid norms, or for few tokens the sums of squares they are made of
   if (op == WM_OP_ROUTER_MIX || op == WM_OP_KV_PROJECT || all || pool)
-    Ly.rinv_mid = take(std::max(2 * (size_t)d.k * N * 4,
-                                all || pool ? wm::few_squares_bytes(make_shape(d)) : 0));
+    Ly.rinv_mid = take(2 * (size_t)d.k * N * 4);
   if (op == WM_OP_KV_PROJECT || op == WM_OP_Q_PROJECT || all || pool || layer)
     Ly.tab = take(N * d.d * 4);
   if (all) Ly.q = take((size_t)d.L * N * d.Hq * d.d * es);
@@ -473,7 +471,10 @@ void run_few_pool(const wm_dims& d, const wm::Shape& sh, const wm_params& P, con
                   hipStream_t s, void* const* events = nullptr) {
   float* part = (float*)at(ws, Ly.rpart);
   bf16* mixed = (bf16*)at(ws, Ly.mixed);
-  float* sq = (float*)at(ws, Ly.rinv_mid);
+  // the mixed channels' sums of squares (k N D bytes) in the place of the folded K/V weights (at
+  // least 4 k Hkv d D), which few tokens do without
+  static_assert(wm::kFewRows <= 4 * 64, "few tokens' sums fit the folded weights' place");
+  float* sq = (float*)at(ws, Ly.wkv);
   wm::launch_few_router(sh, router_layers(d).v[0], H, (const bf16*)P.g_pre,
                         (const bf16*)P.W_alpha, part, s);
   if (events) (void)hipEventRecord((hipEvent_t)events[2], s);

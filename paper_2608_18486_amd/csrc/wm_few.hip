@@ -432,10 +432,6 @@ size_t few_router_bytes(const Shape& sh) {
              ? (size_t)sh.Lp * sh.N() * 2 * sh.k * sh.L * sizeof(float) : 0;
 }
 
-size_t few_squares_bytes(const Shape& sh) {
-  return few_tokens(sh) ? 2ul * sh.k * sh.N() * (sh.D / 8) * sizeof(float) : 0;
-}
-
 void launch_few_router(const Shape& sh, int s0, const bf16* H, const bf16* g_pre,
                        const bf16* W_alpha, float* part, hipStream_t s) {
   if (sh.router_mode == 1) return;  // static weights: no router

@@ -103,9 +103,8 @@ void launch_q_layers(const Shape& sh, const T* H, const float* rinv, const T* g_
 constexpr int kFewRows = 32;
 bool few_tokens(const Shape& sh);
 size_t few_router_bytes(const Shape& sh);
-// The mix also writes its channels' fp32 sums of squares (few_squares_bytes) for the mid norm;
+// The mix also writes its channels' fp32 sums of squares, sq [2][k][N][D / 8], for the mid norm;
 // without them (sq null) launch_few_kv takes the norm from the bf16 channels.
-size_t few_squares_bytes(const Shape& sh);
 void launch_few_router(const Shape& sh, int s0, const bf16* H, const bf16* g_pre,
                        const bf16* W_alpha, float* part, hipStream_t s);
 void launch_few_mix(const Shape& sh, const bf16* H, const bf16* g_pre, const bf16* b_alpha,

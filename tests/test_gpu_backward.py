@@ -21,10 +21,10 @@ pytestmark = pytest.mark.gpu
 def test_channel_attend_backward(wm, T_new, ctx, mask_mode, d, Hq, Hkv, B):
     """B = 4 with Hkv = 2 gives 24 slices (channel, sequence, KV head): with their few slot
     tiles, the slot-major grid takes each XCD's heavy tiles first (slices a multiple of 8);
-    Hkv = 3 at B = 4 does not divide and keeps the slice-major order. The query side: 32-row
-    tiles whose four waves cut the slots up to one of them per CU at head dim 96 (B = 2 at
-    T_new = 40 and 70: 120, 180) and two at 64, two waves up to three per CU at 96 (B = 4 at
-    T_new = 40 and 70: 240, 360; B = 9 at 40: 540), rows split among the waves past that (B = 9
+    Hkv = 3 at B = 4 does not divide and keeps the slice-major order. The query side, by its tiles
+    of 32 rows: four waves cut the slots up to one tile per CU at head dim 96 (B = 2 and 4 at
+    T_new = 40: 120, 240) and two at 64 (B = 9 at T_new = 40: 360), two waves up to three per CU at
+    96 (B = 4 at T_new = 70: 360; B = 9 at 40: 540), rows split among the waves past that (B = 9
     at T_new = 70 and 300: 540 at head dim 64, 810 at 96, and more), with a cached context too."""
     w = synth.small("bwd_d%d" % d, B=B, T_new=T_new, L=5, k=3, D=64, Hq=Hq, Hkv=Hkv, d=d,
                     ctx=ctx + T_new, dtype="bf16", chan_map=[2, 0, 2, 2, 0])

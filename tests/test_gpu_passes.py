@@ -271,7 +271,8 @@ def test_prefill_passes_paper_shape(wm, mix_mode, passes):
 def test_few_token_groups_leave_out_the_folds(wm, backward):
     """Groups of at most 32 bf16 tokens read the weights as given: the folded router and K/V
     weights (and, where no gradient recomputes the queries, the folded query weights) are not
-    made, so that much of a workspace of all ones stays as it was."""
+    made, so that much of a workspace of all ones stays as it was, less the sums of squares that
+    take the place of the K/V weights (2 k N D / 8 floats)."""
     w = synth.small("few_groups", B=2, T_new=64, L=5, k=3, D=256, Hq=4, Hkv=2, d=64, ctx=0,
                     dtype="bf16")
     g = 8
@@ -284,6 +285,7 @@ def test_few_token_groups_leave_out_the_folds(wm, backward):
     ws = torch.full((n,), 255, dtype=torch.uint8, device="cuda")
     Lp = (w.L + w.p - 1) // w.p
     folds = 2 * (2 * w.k * w.L * Lp * w.D + 2 * w.k * w.Hkv * w.d * w.D)
+    folds -= w.k * w.B * (w.T_new // g) * w.D
     if backward:
         grads = {m: torch.zeros(t.shape, device="cuda") for m, t in P.items()}
         dX, dW_o = torch.zeros(X.shape, device="cuda"), torch.zeros(W_o.shape, device="cuda")
