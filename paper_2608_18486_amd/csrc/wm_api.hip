@@ -478,8 +478,7 @@ void run_few_pool(const wm_dims& d, const wm::Shape& sh, const wm_params& P, con
   wm::launch_few_router(sh, router_layers(d).v[0], H, (const bf16*)P.g_pre,
                         (const bf16*)P.W_alpha, part, s);
   if (events) (void)hipEventRecord((hipEvent_t)events[2], s);
-  wm::launch_few_mix(sh, H, (const bf16*)P.g_pre, (const bf16*)P.b_alpha, part, mixed, sq,
-                     s);
+  wm::launch_few_mix(sh, H, (const bf16*)P.g_pre, (const bf16*)P.b_alpha, part, mixed, sq, s);
   if (events) (void)hipEventRecord((hipEvent_t)events[3], s);
   wm::launch_few_kv(sh, mixed, sq, (const bf16*)P.g_mid, (const bf16*)P.Wk,
                     (const bf16*)P.Wv, (const bf16*)P.g_knorm, ctx_len, Kc, Vc, s);

@@ -1185,9 +1185,10 @@ void launch_attend_prefill(const Shape& sh, const LayerTable& chan_map, const T*
     // tile walks the last one's range, so tiles of half the queries of two heads idle less,
     // and with the long ones first a CU pairs a long and a short one (64 sequences x 128
     // queries of a group of 16 over 2048 slots, 6/3 heads of 96: the 256 calls of four passes
-    // over four layers 13.8 -> 11.6 ms; in tile order 13.7). Heads of 64, one call, us: 8/4, 64 x 128
-    // queries of 16 groups 43.6 -> 36.1, 16 x 512 of 4 36.6 -> 30.9; 16/4, 64 x 64 of 16 37.7 ->
-    // 30.4, 32 x 256 of 8 68.3 -> 69.0; 32/8, 64 x 40 of 4 25.5 -> 18.4, 40 x 65 of 8 32.6 -> 33.1.
+    // over four layers 13.8 -> 11.6 ms; in tile order 13.7). Heads of 64, one call, us: 8/4, 64 x
+    // 128 queries of 16 groups 43.6 -> 36.1, 16 x 512 of 4 36.6 -> 30.9; 16/4, 64 x 64 of 16 37.7
+    // -> 30.4, 32 x 256 of 8 68.3 -> 69.0; 32/8, 64 x 40 of 4 25.5 -> 18.4, 40 x 65 of 8 32.6 ->
+    // 33.1.
     long wgs = tiles;
     const bool pair = !doc && ad.nsplit == 1 && sh.gs >= 4 && sh.Hq / sh.Hkv % 2 == 0;
     if (pair) {
