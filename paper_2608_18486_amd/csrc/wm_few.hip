@@ -306,7 +306,8 @@ __global__ __launch_bounds__(64 * kFewWaves) void few_router_kernel(
 // the bias), the weights (mask, softmax), their products with 1 / RMS of the states, and the
 // mixed channels of both branches, all in fp32, and for the mid norm the sums of squares of
 // every eight columns before their rounding to bf16 (as the many-token mix takes them; 0.3 to
-// 1.2 us a pool more than the sums of the rounded ones, mostly at 32 tokens). A thread makes kFewJc channels of 8 columns.
+// 1.2 us a pool more than the sums of the rounded ones, mostly at 32 tokens). A thread makes
+// kFewJc channels of 8 columns.
 constexpr int kFewJc = 4;
 
 __global__ __launch_bounds__(256) void few_mix_kernel(const bf16* H, const bf16* g_pre,
@@ -455,8 +456,8 @@ void launch_few_mix(const Shape& sh, const bf16* H, const bf16* g_pre, const bf1
 }
 
 void launch_few_kv(const Shape& sh, const bf16* mixed, const float* sq, const bf16* g_mid,
-                   const bf16* Wk, const bf16* Wv, const bf16* g_knorm, const int32_t* ctx_len, bf16* Kc,
-                   bf16* Vc, hipStream_t s) {
+                   const bf16* Wk, const bf16* Wv, const bf16* g_knorm, const int32_t* ctx_len,
+                   bf16* Kc, bf16* Vc, hipStream_t s) {
   const long D = sh.D;
   FewProj a{mixed, (long)sh.N() * D, D, Wk, Wv, sh.k, g_mid, sq, g_knorm, sh.N(), sh.D, sh.Hkv,
             sh.T_new, sh.B, sh.gs, sh.gq, ctx_len, sh.ctx_hi, sh.eps, {}, Kc, Vc, sh.S_cap};

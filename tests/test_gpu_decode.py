@@ -115,8 +115,9 @@ def test_streamed_cache(wm, d, k, Hq, Hkv, B, T_new, ctx, waves, docs):
 @pytest.mark.parametrize("B,ctx", [(1, 8191), (2, 4000)])
 def test_one_layer_splits_its_own_channel(wm, k, B, ctx):
     """One layer reads one channel of the cache: its slots are split for that channel's
-    workgroups alone (until there are 512 of them, at 256 slots or more each), however many channels have no reader in the call. The ranges
-    are counted by the partial states written into a workspace of all ones."""
+    workgroups alone (until there are 512 of them, at 256 slots or more each), however many
+    channels have no reader in the call. The ranges are counted by the partial states written
+    into a workspace of all ones."""
     L, Hq, d = 12, 16, 64
     w = synth.small("one_layer", B=B, T_new=1, L=L, k=k, D=64, Hq=Hq, Hkv=Hq, d=d, ctx=ctx + 1,
                     dtype="bf16", chan_map=[0] * L)
